@@ -50,6 +50,27 @@ __device__ __forceinline__ void clover_acc(const SC* __restrict__ Cb, int bvol, 
   }
 }
 
+// w += C_chi v for one chirality of one site; c points at the site's first pair
+// of that chirality, pairs `stride` apart.
+template <typename T, typename SC>
+__device__ __forceinline__ void clover_chi(const SC* __restrict__ c, int stride, const cplx<T> v[6], cplx<T> w[6]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const cplx<T> d = ld<T>(c + q * stride);
+    w[2 * q] += d.re * v[2 * q];
+    w[2 * q + 1] += d.im * v[2 * q + 1];
+  }
+  int q = 3;
+#pragma unroll
+  for (int i = 0; i < 6; ++i)
+#pragma unroll
+    for (int j = i + 1; j < 6; ++j) {
+      const cplx<T> o = ld<T>(c + (q++) * stride);
+      w[i] += o * v[j];
+      w[j] += cdot(o, v[i]);
+    }
+}
+
 // y += s * C x for one site, with x read through xin(comp) one chirality at
 // a time (fewer live registers than clover_acc).
 template <typename T, typename SC, typename XF>

@@ -1,0 +1,289 @@
+// The Wilson-Dirac operator with two lanes per site (included by k_dslash.hip).
+//
+// A hop's half spinor has two rows (upper spin components 0 and 1) that the
+// link multiplies independently, and row r needs only spins r and one of the
+// lower two (3 - r for x and y, 2 + r for z and t). So each site is handled by
+// two lanes, 32 apart in one wavefront, one row each: no projection and no
+// spinor read is done twice, the two lanes' reads of a link entry are one
+// request, and a lane holds half the accumulators. The lower components that
+// row r's hops rebuild are spin 3 - r (x, y hops) and spin 2 + r (z, t hops);
+// the two lanes exchange the x/y sum once at the end and lane r stores spins r
+// and 2 + r.
+//
+// As in the one-lane form the block's spinor is staged in LDS, every link is
+// read once by its own site, and U_mu(n)^+ (1 + g_mu) psi(n) is handed over to
+// site n + mu through LDS.
+//
+// CANON: x, y and b in the canonical layout (12 contiguous complex numbers per
+// site), so that an application on caller fields needs no packing pass: packing,
+// the operator on the internal layout and unpacking moved 2.7 times the bytes
+// (32^3x64, 12 right-hand sides: 8931 -> 5330 us per application; 8^4: 22.5 ->
+// 13.5 us, one launch for three and no allocation).
+//
+// Bound: memory. At 12 right-hand sides the launch moves about 0.8 KB per site
+// and right-hand side beyond the L2 (spinor in and out, faces, links shared).
+#pragma once
+
+#include "dw_clover.hpp"
+#include "dw_internal.hpp"
+#include "dw_stencil.hpp"
+
+namespace dw {
+
+namespace rows {
+
+// projection coefficient of hop (MU, forward) for row r: i sigma (IMAG) or sigma
+template <int MU>
+constexpr bool kImag = MU == 0 || MU == 2;
+
+// p + alpha q with alpha = sigma (i sigma if IMAG)
+template <bool IMAG, typename T>
+__device__ __forceinline__ cplx<T> proj1(cplx<T> p, T sg, cplx<T> q) {
+  if constexpr (IMAG) return mk<T>(fma(-sg, q.im, p.re), fma(sg, q.re, p.im));
+  else return mk<T>(fma(sg, q.re, p.re), fma(sg, q.im, p.im));
+}
+// acc += conj(alpha) g
+template <bool IMAG, typename T>
+__device__ __forceinline__ void rec1(cplx<T>& acc, T sg, cplx<T> g) {
+  if constexpr (IMAG) {
+    acc.re = fma(sg, g.im, acc.re);
+    acc.im = fma(-sg, g.re, acc.im);
+  } else {
+    acc.re = fma(sg, g.re, acc.re);
+    acc.im = fma(sg, g.im, acc.im);
+  }
+}
+// g = W h (DAG false) or W^+ h
+template <bool DAG, typename T>
+__device__ __forceinline__ void mul1(const cplx<T> w[9], const cplx<T> h[3], cplx<T> g[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    cplx<T> s = mk<T>(0, 0);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      if constexpr (DAG) s += cdot(w[b * 3 + a], h[b]);
+      else s += w[a * 3 + b] * h[b];
+    }
+    g[a] = s;
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ T other_row(T v) { return __shfl_xor(v, 32, 64); }
+template <typename T>
+__device__ __forceinline__ cplx<T> other_row(cplx<T> v) { return mk<T>(other_row(v.re), other_row(v.im)); }
+
+template <typename T, typename SX, typename SG>
+struct Ctx {
+  const Geom& g;
+  int b, l, r;         // block, local site, row
+  bool active;
+  T rs;                // +1 for row 0, -1 for row 1
+  const int* bc;
+  const int* lc;
+  long long n;         // canonical site (CANON)
+  const SX* xr;
+  const SX* xsh;       // LDS: block spinor [12][bvol]
+  cplx<T>* pb;         // LDS: handed-over half spinors [6][bvol]
+  const SG* U;
+};
+
+// spinor component k of the site in neighbouring block position c2/nl
+// (internal) or at canonical site nn
+template <bool CANON, typename T, typename SX, typename SG>
+__device__ __forceinline__ cplx<T> face(const Ctx<T, SX, SG>& c, int nb, int nl, long long nn, int k) {
+  if constexpr (CANON) return ld<T>(c.xr + nn * 12 + k);
+  else return ld<T>(c.xr + spinor_index(c.g, nb, k, nl));
+}
+
+template <int MU, bool CANON, typename T, typename SX, typename SG>
+__device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx<T> low[3]) {
+  constexpr bool IM = kImag<MU>;
+  const Geom& g = c.g;
+  const int bvol = g.bvol, l = c.l, r = c.r;
+  const int st = g.lstride[MU];
+  // alpha of the forward hop is sg (times i for x and z): +i, +-1, +-i, -1
+  const T sg = MU == 0 ? (T)1 : MU == 3 ? (T)-1 : c.rs;
+  const int ks = 3 * r, kp = MU < 2 ? 9 - 3 * r : 6 + 3 * r;
+  long long cst = 1;  // canonical site stride
+  if constexpr (CANON) {
+#pragma unroll
+    for (int d = 0; d < MU; ++d) cst *= g.L[d];
+  }
+  cplx<T> h[3], v[3];
+  if (c.active) {
+    cplx<T> w[9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) w[e] = ld<T>(c.U + gauge_index(g, c.b, MU, e, l));
+    // U_mu(n)^+ (1 + g_mu) psi(n) for site n + mu
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      h[a] = proj1<IM, T>(ld<T>(c.xsh + (ks + a) * bvol + l), -sg, ld<T>(c.xsh + (kp + a) * bvol + l));
+    mul1<true, T>(w, h, v);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) c.pb[(ks + a) * bvol + l] = v[a];
+    // forward hop (1 - g_mu) U_mu(n) psi(n + mu)
+    if (c.lc[MU] < g.B[MU] - 1) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        h[a] = proj1<IM, T>(ld<T>(c.xsh + (ks + a) * bvol + l + st), sg, ld<T>(c.xsh + (kp + a) * bvol + l + st));
+    } else {
+      const bool wrap = c.bc[MU] + 1 == g.N[MU];
+      int nb = 0;
+      long long nn = 0;
+      if constexpr (CANON) {
+        nn = c.n + (wrap ? cst * (1 - (long long)g.L[MU]) : cst);
+      } else {
+        int c2[4] = {c.bc[0], c.bc[1], c.bc[2], c.bc[3]};
+        c2[MU] = wrap ? 0 : c.bc[MU] + 1;
+        nb = encode_block(g, c2);
+      }
+      const int nl = l - (g.B[MU] - 1) * st;
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        h[a] = proj1<IM, T>(face<CANON>(c, nb, nl, nn, ks + a), sg, face<CANON>(c, nb, nl, nn, kp + a));
+    }
+    mul1<false, T>(w, h, v);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      up[a] += v[a];
+      rec1<IM, T>(low[a], sg, v[a]);
+    }
+  }
+  __syncthreads();
+  if (c.active) {
+    if (c.lc[MU] > 0) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) v[a] = c.pb[(ks + a) * bvol + l - st];
+    } else {
+      const bool wrap = c.bc[MU] == 0;
+      int c2[4] = {c.bc[0], c.bc[1], c.bc[2], c.bc[3]};
+      c2[MU] = wrap ? g.N[MU] - 1 : c.bc[MU] - 1;
+      const int nb = encode_block(g, c2), nl = l + (g.B[MU] - 1) * st;
+      const long long nn = CANON ? c.n + (wrap ? cst * ((long long)g.L[MU] - 1) : -cst) : 0;
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        h[a] = proj1<IM, T>(face<CANON>(c, nb, nl, nn, ks + a), -sg, face<CANON>(c, nb, nl, nn, kp + a));
+      cplx<T> w[9];
+#pragma unroll
+      for (int e = 0; e < 9; ++e) w[e] = ld<T>(c.U + gauge_index(g, nb, MU, e, nl));
+      mul1<true, T>(w, h, v);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      up[a] += v[a];
+      rec1<IM, T>(low[a], -sg, v[a]);
+    }
+  }
+  if constexpr (MU < 3) __syncthreads();
+}
+
+}  // namespace rows
+
+// per-right-hand-side gate and device-side mass (both optional)
+struct DCtl {
+  const int* gate = nullptr;
+  int gstride = 0;
+  const double* dmass = nullptr;
+};
+
+// threads of a workgroup: a block's sites in groups of 32, two lanes each
+inline int rows_threads(const Geom& g) { return ((g.bvol + 31) / 32) * 64; }
+template <typename T, typename SX>
+size_t rows_lds(const Geom& g) {
+  return (((size_t)12 * g.bvol * sizeof(SX) + 15) & ~(size_t)15) + (size_t)6 * g.bvol * sizeof(cplx<T>);
+}
+// blocks the two-lane form takes: one workgroup per block
+template <typename T, typename SX>
+bool rows_fits(const Geom& g) { return rows_threads(g) <= 1024 && rows_lds<T, SX>(g) <= 160 * 1024; }
+
+// MODE 0: y = scale * D x; MODE 1: y = b - scale * D x
+template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV, bool CANON>
+__global__ void __launch_bounds__(1024)
+    k_dslash_rows(Geom g, T diag, const SX* __restrict__ x, T scale, const SG* __restrict__ U, SY* __restrict__ y,
+                  const SY* __restrict__ bsrc, long long xs, long long ys, int nr, const int* __restrict__ rlist,
+                  const SG* __restrict__ Cl, DCtl dc) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  SX* xsh = reinterpret_cast<SX*>(smem);
+  cplx<T>* pb = reinterpret_cast<cplx<T>*>(smem + (((size_t)12 * g.bvol * sizeof(SX) + 15) & ~(size_t)15));
+  // work item -> (block, RHS) with the RHS fastest: workgroups that read the
+  // same links run together on one XCD
+  const int wi = xcd_remap(blockIdx.x, g.nblk * nr);
+  if (wi < 0) return;  // uniform for the workgroup
+  const int b = wi / nr;
+  const int rhs = rlist ? rlist[wi - b * nr] : wi - b * nr;
+  if (dc.gate && dc.gate[(long long)rhs * dc.gstride] == 0) return;  // uniform for the workgroup
+  if (dc.dmass) diag = (T)(4.0 + *dc.dmass);
+  const int l = (threadIdx.x >> 6) * 32 + (threadIdx.x & 31);
+  const int r = (threadIdx.x >> 5) & 1;
+  const bool active = l < g.bvol;
+  const SX* xr = x + (long long)rhs * xs;
+  SY* yr = y + (long long)rhs * ys;
+  int bc[4], lc[4] = {0, 0, 0, 0};
+  decode_block(g, b, bc);
+  long long n = 0;
+  auto own = [&](int k) { return CANON ? n * 12 + k : spinor_index(g, b, k, l); };
+  if (active) {
+    decode_local(g, l, lc);
+    if constexpr (CANON)
+      n = bc[0] * g.B[0] + lc[0] +
+          (long long)g.L[0] * (bc[1] * g.B[1] + lc[1] +
+                               (long long)g.L[1] * (bc[2] * g.B[2] + lc[2] + (long long)g.L[2] * (bc[3] * g.B[3] + lc[3])));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      xsh[(3 * r + k) * g.bvol + l] = xr[own(3 * r + k)];
+      xsh[(6 + 3 * r + k) * g.bvol + l] = xr[own(6 + 3 * r + k)];
+    }
+  }
+  __syncthreads();
+  const rows::Ctx<T, SX, SG> c{g, b, l, r, active, r ? (T)-1 : (T)1, bc, lc, n, xr, xsh, pb, U};
+  cplx<T> up[3], lowxy[3], lowzt[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) up[a] = lowxy[a] = lowzt[a] = mk<T>(0, 0);
+  rows::dir<0, CANON>(c, up, lowxy);
+  rows::dir<1, CANON>(c, up, lowxy);
+  rows::dir<2, CANON>(c, up, lowzt);
+  rows::dir<3, CANON>(c, up, lowzt);
+  // spin 2 + r: this lane's z/t sum and the other lane's x/y sum
+#pragma unroll
+  for (int a = 0; a < 3; ++a) lowzt[a] += rows::other_row(lowxy[a]);
+  cplx<T> cu[3], cd[3];
+  if constexpr (CLOV) {
+    // lane r takes chirality r (spins 2r and 2r + 1) and the two lanes swap
+    // the spin that the other one stores
+    cplx<T> w[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) w[i] = mk<T>(0, 0);
+    if (active) {
+      cplx<T> v[6];
+#pragma unroll
+      for (int i = 0; i < 6; ++i) v[i] = ld<T>(xsh + (6 * r + i) * g.bvol + l);
+      clover_chi<T>(Cl + ((long long)b * kCloverPairs + 18 * r) * g.bvol + l, g.bvol, v, w);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const cplx<T> give = r ? w[a] : w[3 + a];
+      const cplx<T> got = rows::other_row(give);
+      cu[a] = r ? got : w[a];
+      cd[a] = r ? w[3 + a] : got;
+    }
+  }
+  if (active) {
+    const T half = (T)0.5;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const int k = 6 * q + 3 * r + a;
+        const cplx<T> psi = ld<T>(xsh + k * g.bvol + l);
+        cplx<T> acc = q ? lowzt[a] : up[a];
+        if constexpr (CLOV) acc -= (T)2 * (q ? cd[a] : cu[a]);
+        cplx<T> d = scale * (diag * psi - half * acc);
+        if constexpr (MODE == 1) d = ld<T>(bsrc + (long long)rhs * ys + own(k)) - d;
+        if constexpr (CANON) st(yr + own(k), d);
+        else st_nt(yr + own(k), d);
+      }
+  }
+}
+
+}  // namespace dw

@@ -224,6 +224,11 @@ dw_status launch_dslash_outer(const Geom& g, double m0, int prec_x, const void* 
                               long long y_rhs_stride, hipStream_t s, const int* rlist = nullptr,
                               const void* C64 = nullptr, const int* gate = nullptr, int gstride = 0,
                               const double* dmass = nullptr);
+// y = D x on canonical FP64 fields, no packing pass; for blocks that
+// dslash_canonical_fits takes
+bool dslash_canonical_fits(const Geom& g);
+dw_status launch_dslash_canonical(const Geom& g, double m0, const double* x, const void* U64, double* y, int nrhs,
+                                  hipStream_t s, const void* C64);
 dw_status launch_dslash_lowp(const Geom& g, double m0, int prec, const void* x, const void* U, void* y, int nrhs,
                              hipStream_t s, const void* C = nullptr);
 // w = D z with FP32 vectors, FP32 links (and clover term) and FP32 arithmetic:

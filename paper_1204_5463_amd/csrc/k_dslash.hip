@@ -8,6 +8,8 @@
 // half spinor that site n + mu needs, and hands it over through LDS
 // (sites on a block's lower face compute theirs from the neighbouring
 // block). Launch order is XCD-aware so neighbouring blocks share an L2.
+// FP64 arithmetic uses two threads per site (dw_dslash_rows.hpp); one thread
+// per site remains for FP32 arithmetic and for FP64 blocks above 512 sites.
 // Blocks whose LDS footprint exceeds the CU's 160 KiB fall back to a
 // gather kernel that reads all neighbours through the caches.
 //
@@ -16,6 +18,7 @@
 // result is written with streaming stores (it is not read again by this
 // launch), which leaves more of the caches to the block faces.
 #include "dw_clover.hpp"
+#include "dw_dslash_rows.hpp"
 #include "dw_internal.hpp"
 #include "dw_stencil.hpp"
 
@@ -151,13 +154,6 @@ __device__ __forceinline__ void blk_dir16(const BlkCtx<float, SX, SG>& c, cplx<f
 }
 
 __host__ __device__ constexpr size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
-
-// per-right-hand-side gate and device-side mass (both optional)
-struct DCtl {
-  const int* gate = nullptr;
-  int gstride = 0;
-  const double* dmass = nullptr;
-};
 
 // CLOV: add the clover term (site-local, dw_clover.hpp) from Cl.
 template <typename T, typename SX, typename SG, typename SY, int MODE, int MAXT, bool CLOV>
@@ -295,13 +291,45 @@ template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV
 dw_status launch_any(const Geom& g, T diag, const SX* x, T scale, const SG* U, SY* y, const SY* b, long long xs,
                      long long ys, int nrhs, const int* rlist, hipStream_t s, const SG* Cl, DCtl dc);
 
+// FP64 arithmetic takes the two-lane form: 118 registers instead of 196, four
+// waves per SIMD instead of two (32^3x64: D x 336 -> 327 us, b - D x 578 ->
+// 564 us in a solve). FP32 arithmetic keeps one lane per site: there the
+// registers do not limit the waves and the two lanes read every link twice
+// (24^3x48, 4 right-hand sides: 280 us with one lane, 348 with two).
+template <typename T>
+constexpr bool kRows = std::is_same<T, double>::value;
+
 dim3 grid_for(const Geom& g, int nrhs) {
   return dim3((unsigned)xcd_grid((int)((g.V + kThreads - 1) / kThreads)), (unsigned)nrhs);
+}
+
+template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV, bool CANON>
+dw_status launch_rows(const Geom& g, T diag, const SX* x, T scale, const SG* U, SY* y, const SY* b, long long xs,
+                      long long ys, int nrhs, const int* rlist, hipStream_t s, const SG* Cl, DCtl dc) {
+  const size_t lds = rows_lds<T, SX>(g);
+  const int threads = rows_threads(g);
+  auto go = [&](auto kernel) -> dw_status {
+    if (lds > 64 * 1024) {
+      hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) {
+        set_error("hipFuncSetAttribute(LDS %zu) failed: %s", lds, hipGetErrorString(e));
+        return DW_EHIP;
+      }
+    }
+    dim3 grid((unsigned)xcd_grid(g.nblk * nrhs), 1);
+    hipLaunchKernelGGL(kernel, grid, threads, lds, s, g, diag, x, scale, U, y, b, xs, ys, nrhs, rlist, Cl, dc);
+    DW_CHECK_LAUNCH();
+    return DW_OK;
+  };
+  return go(k_dslash_rows<T, SX, SG, SY, MODE, CLOV, CANON>);
 }
 
 template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV>
 dw_status launch_any(const Geom& g, T diag, const SX* x, T scale, const SG* U, SY* y, const SY* b, long long xs,
                      long long ys, int nrhs, const int* rlist, hipStream_t s, const SG* Cl, DCtl dc) {
+  if constexpr (kRows<T>)
+    if (rows_fits<T, SX>(g))
+      return launch_rows<T, SX, SG, SY, MODE, CLOV, false>(g, diag, x, scale, U, y, b, xs, ys, nrhs, rlist, s, Cl, dc);
   const size_t lds = blk_lds<T, SX>(g);
   const int threads = ((g.bvol + 63) / 64) * 64;
   if (lds <= 160 * 1024) {
@@ -370,6 +398,24 @@ dw_status launch_dslash_outer(const Geom& g, double m0, int prec_x, const void* 
   kt.done((double)g.V * nrhs *
               (12.0 * pair_bytes(prec_x) + 36 * 16 + 12 * 16 + (mode == 1 ? 12 * 16 : 0) + (Cg ? kCloverPairs * 16 : 0)),
           (double)g.V * nrhs * (kFlopsPerSite + (Cg ? kCloverFlops : 0.0)));
+  return DW_OK;
+}
+
+bool dslash_canonical_fits(const Geom& g) { return rows_fits<double, s64>(g); }
+
+dw_status launch_dslash_canonical(const Geom& g, double m0, const double* x, const void* U64, double* y, int nrhs,
+                                  hipStream_t s, const void* C64) {
+  if (nrhs < 1) return DW_OK;
+  const long long n = g.V * 12;
+  KTimer kt(DW_K_DSLASH_F64, s);
+  if (C64)
+    DW_TRY((launch_rows<double, s64, s64, s64, 0, true, true>(g, 4.0 + m0, (const s64*)x, 1.0, (const s64*)U64, (s64*)y,
+                                                              nullptr, n, n, nrhs, nullptr, s, (const s64*)C64, DCtl{})));
+  else
+    DW_TRY((launch_rows<double, s64, s64, s64, 0, false, true>(g, 4.0 + m0, (const s64*)x, 1.0, (const s64*)U64, (s64*)y,
+                                                               nullptr, n, n, nrhs, nullptr, s, nullptr, DCtl{})));
+  kt.done((double)g.V * nrhs * (60.0 + (C64 ? kCloverPairs : 0)) * 16,
+          (double)g.V * nrhs * (kFlopsPerSite + (C64 ? kCloverFlops : 0.0)));
   return DW_OK;
 }
 

@@ -297,6 +297,8 @@ dw_status dw_apply(dw_field f, double m0, const double* x, double* y, int32_t nr
   DW_TRY(check_device(f->ctx));
   ProfScope ps(f->ctx);
   const Geom& g = f->g;
+  if (dslash_canonical_fits(g))
+    return launch_dslash_canonical(g, m0, x, f->U[DW_PREC_F64], y, nrhs, stream, f->C[DW_PREC_F64]);
   const size_t n = (size_t)g.V * 12;
   DevBuf xi, yi;
   DW_TRY(xi.alloc(f->ctx, n * 16 * nrhs, stream));
@@ -335,6 +337,8 @@ dw_status dw_apply_noalloc(dw_field f, double m0, const double* x, double* y, in
     return DW_EHIP;
   }
   ProfScope ps(f->ctx);
+  if (dslash_canonical_fits(g))
+    return launch_dslash_canonical(g, m0, x, f->U[DW_PREC_F64], y, nrhs, stream, f->C[DW_PREC_F64]);
   const long long n = g.V * 12;
   void* xi = base;
   double* yi = (double*)(base + yofs);
