@@ -64,6 +64,47 @@ __host__ __device__ __forceinline__ cplx<T> mul_i(cplx<T> a) { return {-a.im, a.
 template <typename T>
 __host__ __device__ __forceinline__ cplx<T> mul_mi(cplx<T> a) { return {a.im, -a.re}; }
 
+// ---- sums over a wavefront ---------------------------------------------------
+// FP64 sums stay in registers: data-parallel-primitive moves instead of LDS
+// permutes (two permutes and a wait on the LDS per step; a chain of six steps
+// took about 700 cycles that way).
+template <int CTRL, int ROWS, bool ZERO>
+__device__ __forceinline__ double dpp64(double old, double v) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(v), CTRL, ROWS, 0xf, ZERO);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(v), CTRL, ROWS, 0xf, ZERO);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// sum over the 64 lanes, in every lane (fixed order: rows of 16, then the rows)
+__device__ __forceinline__ double wave_total(double a) {
+  a += dpp64<0x111, 0xf, false>(0.0, a);  // row_shr:1
+  a += dpp64<0x112, 0xf, false>(0.0, a);  // row_shr:2
+  a += dpp64<0x114, 0xf, false>(0.0, a);  // row_shr:4
+  a += dpp64<0x118, 0xf, false>(0.0, a);  // row_shr:8
+  a += dpp64<0x142, 0xa, false>(0.0, a);  // row_bcast:15 into rows 1 and 3
+  a += dpp64<0x143, 0xc, false>(0.0, a);  // row_bcast:31 into rows 2 and 3
+  return lane_value(a, 63);
+}
+// largest value over the 64 lanes, in every lane
+__device__ __forceinline__ double wave_largest(double a) {
+  a = fmax(a, dpp64<0x111, 0xf, false>(a, a));
+  a = fmax(a, dpp64<0x112, 0xf, false>(a, a));
+  a = fmax(a, dpp64<0x114, 0xf, false>(a, a));
+  a = fmax(a, dpp64<0x118, 0xf, false>(a, a));
+  a = fmax(a, dpp64<0x142, 0xa, false>(a, a));
+  a = fmax(a, dpp64<0x143, 0xc, false>(a, a));
+  return lane_value(a, 63);
+}
+// sum over each group of four lanes, in all of them
+__device__ __forceinline__ double quad_total(double a) {
+  a += dpp64<0xb1, 0xf, true>(0.0, a);  // lanes 1, 0, 3, 2
+  a += dpp64<0x4e, 0xf, true>(0.0, a);  // lanes 2, 3, 0, 1
+  return a;
+}
+
 // ---- storage formats -------------------------------------------------------
 
 struct __attribute__((aligned(16))) s64 { double x, y; };

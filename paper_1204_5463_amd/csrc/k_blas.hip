@@ -25,11 +25,7 @@ constexpr int kRotMax = 24;   // output columns of one rotation pass
 constexpr int kGsCols = 8;    // columns per pass of the Gram-Schmidt reduction
 constexpr int kUpd = 8;       // columns loaded together by the Gram-Schmidt update
 
-__device__ __forceinline__ double wsum(double a) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) a += __shfl_xor(a, off, kWave);
-  return a;
-}
+__device__ __forceinline__ double wsum(double a) { return wave_total(a); }
 
 // partials[c * gridDim.x + block] = sum over this block's elements of conj(V_c) w
 template <typename SV>
@@ -75,45 +71,44 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// out[c*ostride] (op 0: =, op 1: +=) sum_g partials[c*G + g]; one wave per column
+// out[c*ostride] (op 0: =, op 1: +=) sum_g partials[c*G + g], one workgroup
+// per column c: its threads take the G partials side by side and the wavefront
+// sums are added in a fixed order. (One workgroup for all columns took 24-32 us
+// at G = 1024 and 40-60 columns, a chain of 16 dependent loads per column.)
 __global__ void __launch_bounds__(kThreads)
     k_reduce(const s64* __restrict__ partials, int G, int ncols, s64* __restrict__ out, int ostride, int op,
              const int* __restrict__ gate, const int* __restrict__ dn, int dmul, int dadd) {
   if (gate && *gate == 0) return;
   if (dn) ncols = dmul * *dn + dadd;
+  const int c = blockIdx.x;
+  if (c >= ncols) return;  // uniform for the workgroup
+  __shared__ double red[kThreads / kWave][2];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  for (int c = wave; c < ncols; c += kThreads / kWave) {
-    double re = 0, im = 0;
-    for (int g = lane; g < G; g += kWave) {
-      re += partials[(long long)c * G + g].x;
-      im += partials[(long long)c * G + g].y;
-    }
-    re = wsum(re);
-    im = wsum(im);
-    if (lane == 0) {
-      s64* o = out + (long long)c * ostride;
-      if (op == 1) {
-        re += o->x;
-        im += o->y;
-      }
-      *o = s64{re, im};
-    }
+  double re = 0, im = 0;
+  for (int g = threadIdx.x; g < G; g += kThreads) {
+    const cplx<double> p = ld<double>(partials + (long long)c * G + g);
+    re += p.re;
+    im += p.im;
   }
-}
-
-// w -= sum_c h[c] V_c   (h on the device)
-template <typename SV>
-__global__ void __launch_bounds__(kThreads)
-    k_sub_cols(const SV* __restrict__ V, long long stride, int ncols, const s64* __restrict__ h, s64* __restrict__ w,
-               long long n) {
-  __shared__ cplx<double> hs[64];
-  for (int c = threadIdx.x; c < ncols; c += kThreads) hs[c] = ld<double>(h + c);
+  re = wsum(re);
+  im = wsum(im);
+  if (lane == 0) {
+    red[wave][0] = re;
+    red[wave][1] = im;
+  }
   __syncthreads();
-  const long long step = (long long)gridDim.x * kThreads;
-  for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n; i += step) {
-    cplx<double> a = ld<double>(w + i);
-    for (int c = 0; c < ncols; ++c) a -= hs[c] * ld<double>(V + c * stride + i);
-    st(w + i, a);
+  if (threadIdx.x == 0) {
+    re = im = 0;
+    for (int q = 0; q < kThreads / kWave; ++q) {
+      re += red[q][0];
+      im += red[q][1];
+    }
+    s64* o = out + (long long)c * ostride;
+    if (op == 1) {
+      re += o->x;
+      im += o->y;
+    }
+    *o = s64{re, im};
   }
 }
 
@@ -198,23 +193,25 @@ __global__ void __launch_bounds__(kThreads)
 // Arnoldi); the per-workgroup sums are combined in double.
 template <bool HU, bool HW, typename SV, typename SW, typename T>
 __global__ void __launch_bounds__(kThreads)
-    k_gs_reduce(const SV* __restrict__ V, long long stride, int c0, int nc, int nv, const SV* __restrict__ u,
-                const SW* __restrict__ w, long long n, int first, s64* __restrict__ partials,
-                const int* __restrict__ gate, const int* __restrict__ dcol, int chunk) {
+    k_gs_reduce(const SV* __restrict__ V, long long stride, int nv, const SV* __restrict__ u,
+                const SW* __restrict__ w, long long n, s64* __restrict__ partials, const int* __restrict__ gate,
+                const int* __restrict__ dcol) {
   constexpr int NA = kGsCols;
   if (gate && *gate == 0) return;
   if (dcol) {
-    // finalising column nv = *dcol against the nv columns before it: the
-    // chunk split of the host-side form, on the device-side count
+    // finalising column nv = *dcol against the nv columns before it
     nv = *dcol;
     u = V + (long long)nv * stride;
-    const int nchunks = nv > 0 ? (nv + NA - 1) / NA : 1;
-    if (chunk >= nchunks) return;
-    const int per = nv > 0 ? (nv + nchunks - 1) / nchunks : 0;
-    c0 = chunk * per;
-    nc = nv - c0 < per ? nv - c0 : per;
-    first = chunk == 0;
   }
+  // the columns in chunks of at most NA, split evenly, one chunk per grid row
+  // (each chunk reads u and w again)
+  const int chunk = blockIdx.y;
+  const int nchunks = nv > 0 ? (nv + NA - 1) / NA : 1;
+  if (chunk >= nchunks) return;
+  const int per = nv > 0 ? (nv + nchunks - 1) / nchunks : 0;
+  const int c0 = chunk * per;
+  const int nc = nv - c0 < per ? nv - c0 : per;
+  const bool first = chunk == 0;
   __shared__ double red[kThreads / kWave][2 * NA + 3][2];
   cplx<T> au[NA], aw[NA], uu = mk<T>(0, 0), uw = mk<T>(0, 0), ww = mk<T>(0, 0);
 #pragma unroll
@@ -279,25 +276,65 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// coef: a[0..nv), b[0..nv), c (slot 2 nv), 1/beta (slot 2 nv + 1, real part).
+// red: a = V^H u [0..nv), b = V^H w [nv..2 nv), u^H u, u^H w, w^H w from
+// gs_reduce. Every workgroup forms the step's coefficients from them itself
+// (beta = sqrt(u^H u - |a|^2), c = (u^H w - a^H b) / beta), the first one also
+// writes them into H: H(0:jcol, jcol-1) += a and H(jcol, jcol-1) = beta where
+// u = V_jcol is finalised (HU), and the first-pass entries b (and c in row
+// jcol) of column jw (HW).
 // HU: V_jcol <- (V_jcol - V a) / beta (in place); HW: wout <- w - V b - c V_jcol,
 // partials[block] = sum |wout|^2 over the block's elements.
 template <bool HU, bool HW, typename SV, typename SW, typename T>
 __global__ void __launch_bounds__(kThreads)
-    k_gs_update(SV* __restrict__ V, long long stride, int nv, int jcol, const SW* __restrict__ w,
-                SV* __restrict__ wout, const s64* __restrict__ coef, long long n, s64* __restrict__ partials,
-                const int* __restrict__ gate, const int* __restrict__ dcol) {
+    k_gs_update(SV* __restrict__ V, long long stride, int nv, int jcol, int jw, const SW* __restrict__ w,
+                SV* __restrict__ wout, const s64* __restrict__ red_in, s64* __restrict__ H, long long n,
+                s64* __restrict__ partials, const int* __restrict__ gate, const int* __restrict__ dcol) {
   if (gate && *gate == 0) return;
   if (dcol) nv = jcol = *dcol;
   __shared__ cplx<T> ca[kMaxM + 1], cb[kMaxM + 1];
   __shared__ double red[kThreads / kWave];
-  for (int c = threadIdx.x; c < nv; c += kThreads) {
-    ca[c] = ld<T>(coef + c);
-    cb[c] = ld<T>(coef + nv + c);
+  cplx<T> cj = mk<T>(0, 0);
+  T invbeta = (T)1;
+  {
+    const int lane = threadIdx.x % kWave;
+    cplx<double> av = mk(0.0, 0.0), bv = mk(0.0, 0.0);
+    if (lane < nv) {  // nv <= kMaxM + 1 < 64
+      if constexpr (HU) av = ld<double>(red_in + lane);
+      if constexpr (HW) bv = ld<double>(red_in + nv + lane);
+    }
+    if (threadIdx.x < nv) {
+      ca[lane] = mk<T>((T)av.re, (T)av.im);
+      cb[lane] = mk<T>((T)bv.re, (T)bv.im);
+    }
+    double beta = 1.0, ib = 1.0;
+    cplx<double> c = mk(0.0, 0.0);
+    if constexpr (HU) {
+      const double b2 = red_in[2 * nv].x - wsum(norm2(av));
+      beta = b2 > 0 ? sqrt(b2) : 0.0;
+      ib = beta > 0 ? 1.0 / beta : 0.0;
+      if constexpr (HW) {
+        const cplx<double> ab = cdot(av, bv);
+        const cplx<double> uw = ld<double>(red_in + 2 * nv + 1);
+        c = ib * mk(uw.re - wsum(ab.re), uw.im - wsum(ab.im));
+      }
+    }
+    cj = mk<T>((T)c.re, (T)c.im);
+    invbeta = (T)ib;
+    if (blockIdx.x == 0 && threadIdx.x < nv) {
+      if constexpr (HU)
+        if (jcol >= 1) {
+          s64* h = H + lane + (long long)(jcol - 1) * kLd;
+          st(h, ld<double>(h) + av);
+        }
+      if constexpr (HW) st(H + lane + (long long)jw * kLd, bv);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if constexpr (HU)
+        if (jcol >= 1) st(H + jcol + (long long)(jcol - 1) * kLd, mk(beta, 0.0));
+      if constexpr (HU && HW) st(H + jcol + (long long)jw * kLd, c);
+    }
   }
   __syncthreads();
-  const cplx<T> cj = ld<T>(coef + 2 * nv);
-  const T invbeta = (T)coef[2 * nv + 1].x;
   double nrm = 0;
   const long long step = (long long)gridDim.x * kThreads;
   for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n; i += step) {
@@ -372,23 +409,10 @@ dw_status blas_dots(int prec_v, const void* V, long long stride, int ncols, cons
     kt.done((double)n * (nc * (double)pair_bytes(prec_v) + 16), (double)n * nc * 8);
   }
   KTimer kr(DW_K_REDUCE, s);
-  hipLaunchKernelGGL(k_reduce, 1, kThreads, 0, s, (const s64*)partials, (int)G, ncols, (s64*)out, ostride, op, gate,
+  hipLaunchKernelGGL(k_reduce, ncols, kThreads, 0, s, (const s64*)partials, (int)G, ncols, (s64*)out, ostride, op, gate,
                      dn, 1, dadd);
   DW_CHECK_LAUNCH();
   kr.done((double)G * ncols * 16, (double)G * ncols * 2);
-  return DW_OK;
-}
-
-dw_status blas_sub_cols(const double* V, long long stride, int ncols, const double* h, double* w, long long n,
-                        hipStream_t s) {
-  if (ncols > 64) {
-    set_error("blas_sub_cols: too many columns");
-    return DW_EINVAL;
-  }
-  KTimer kt(DW_K_SUBCOLS, s);
-  hipLaunchKernelGGL(k_sub_cols<s64>, grid_for(n), kThreads, 0, s, (const s64*)V, stride, ncols, (const s64*)h, (s64*)w, n);
-  DW_CHECK_LAUNCH();
-  kt.done((double)n * (ncols + 2) * 16, (double)n * ncols * 8);
   return DW_OK;
 }
 
@@ -449,32 +473,25 @@ dw_status gs_reduce_t(const SV* Vp, long long stride, int nv, const SV* up, cons
                       double* partials, double* out, hipStream_t s, const int* gate, const int* dcol) {
   const bool hu = up != nullptr || dcol != nullptr, hw = wp != nullptr;
   const unsigned G = grid_for(n);
-  // the columns in as few passes as possible, split evenly (u and w are
-  // re-read by every pass); with dcol the device picks the split of its
-  // count and nv bounds it
-  const int nchunks = nv > 0 ? (nv + kGsCols - 1) / kGsCols : 1;
-  const int per = nv > 0 ? (nv + nchunks - 1) / nchunks : 0;
-  for (int q = 0; q < nchunks; ++q) {
-    const int c0 = q * per;
-    const int nc = nv - c0 < per ? nv - c0 : per;
-    KTimer kt(DW_K_DOTS, s);
-    s64* part = (s64*)partials;
-    if (hu && hw)
-      hipLaunchKernelGGL((k_gs_reduce<true, true, SV, SW, T>), G, kThreads, 0, s, Vp, stride, c0, nc, nv, up, wp, n, q == 0,
-                         part, gate, dcol, q);
-    else if (hu)
-      hipLaunchKernelGGL((k_gs_reduce<true, false, SV, SW, T>), G, kThreads, 0, s, Vp, stride, c0, nc, nv, up, wp, n,
-                         q == 0, part, gate, dcol, q);
-    else
-      hipLaunchKernelGGL((k_gs_reduce<false, true, SV, SW, T>), G, kThreads, 0, s, Vp, stride, c0, nc, nv, up, wp, n,
-                         q == 0, part, gate, dcol, q);
-    DW_CHECK_LAUNCH();
-    kt.done((double)n * (sizeof(SV) * (nc + (hu ? 1 : 0)) + (hw ? sizeof(SW) : 0)),
-            (double)n * 8 * nc * ((hu ? 1 : 0) + (hw ? 1 : 0)));
-  }
+  const int nchunks = nv > 0 ? (nv + kGsCols - 1) / kGsCols : 1;  // with dcol nv bounds the device's count
+  const dim3 grid(G, (unsigned)nchunks);
+  KTimer kt(DW_K_DOTS, s);
+  s64* part = (s64*)partials;
+  if (hu && hw)
+    hipLaunchKernelGGL((k_gs_reduce<true, true, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, part, gate,
+                       dcol);
+  else if (hu)
+    hipLaunchKernelGGL((k_gs_reduce<true, false, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, part, gate,
+                       dcol);
+  else
+    hipLaunchKernelGGL((k_gs_reduce<false, true, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, part, gate,
+                       dcol);
+  DW_CHECK_LAUNCH();
+  kt.done((double)n * (sizeof(SV) * (nv + (hu ? 1 : 0)) + (hw ? sizeof(SW) : 0)),
+          (double)n * 8 * nv * ((hu ? 1 : 0) + (hw ? 1 : 0)));
   KTimer kr(DW_K_REDUCE, s);
-  hipLaunchKernelGGL(k_reduce, 1, kThreads, 0, s, (const s64*)partials, (int)G, 2 * nv + 3, (s64*)out, 1, 0, gate,
-                     dcol, 2, 3);
+  hipLaunchKernelGGL(k_reduce, 2 * nv + 3, kThreads, 0, s, (const s64*)partials, (int)G, 2 * nv + 3, (s64*)out, 1, 0,
+                     gate, dcol, 2, 3);
   DW_CHECK_LAUNCH();
   kr.done((double)G * (2 * nv + 3) * 16, 0);
   return DW_OK;
@@ -498,49 +515,44 @@ dw_status gs_reduce(int prec_v, const void* V, long long stride, int nv, const v
 }
 
 template <typename SV, typename SW, typename T>
-dw_status gs_update_t(SV* Vp, long long stride, int nv, int jcol, const SW* w, SV* wout, const double* coef,
-                      long long n, double* partials, double* nrm2, hipStream_t s, const int* gate, const int* dcol) {
+dw_status gs_update_t(SV* Vp, long long stride, int nv, int jcol, int jw, const SW* w, SV* wout, const double* red,
+                      double* H, long long n, double* partials, hipStream_t s, const int* gate, const int* dcol) {
   const bool hu = jcol >= 0 || dcol != nullptr, hw = w != nullptr;
   const unsigned G = grid_for(n);
   KTimer kt(DW_K_SUBCOLS, s);
   if (hu && hw)
-    hipLaunchKernelGGL((k_gs_update<true, true, SV, SW, T>), G, kThreads, 0, s, Vp, stride, nv, jcol, w, wout,
-                       (const s64*)coef, n, (s64*)partials, gate, dcol);
+    hipLaunchKernelGGL((k_gs_update<true, true, SV, SW, T>), G, kThreads, 0, s, Vp, stride, nv, jcol, jw, w, wout,
+                       (const s64*)red, (s64*)H, n, (s64*)partials, gate, dcol);
   else if (hu)
-    hipLaunchKernelGGL((k_gs_update<true, false, SV, SW, T>), G, kThreads, 0, s, Vp, stride, nv, jcol, w, wout,
-                       (const s64*)coef, n, (s64*)partials, gate, dcol);
+    hipLaunchKernelGGL((k_gs_update<true, false, SV, SW, T>), G, kThreads, 0, s, Vp, stride, nv, jcol, jw, w, wout,
+                       (const s64*)red, (s64*)H, n, (s64*)partials, gate, dcol);
   else
-    hipLaunchKernelGGL((k_gs_update<false, true, SV, SW, T>), G, kThreads, 0, s, Vp, stride, nv, jcol, w, wout,
-                       (const s64*)coef, n, (s64*)partials, gate, dcol);
+    hipLaunchKernelGGL((k_gs_update<false, true, SV, SW, T>), G, kThreads, 0, s, Vp, stride, nv, jcol, jw, w, wout,
+                       (const s64*)red, (s64*)H, n, (s64*)partials, gate, dcol);
   DW_CHECK_LAUNCH();
   kt.done((double)n * (sizeof(SV) * (nv + (hu ? 2 : 0) + (hw ? 1 : 0)) + (hw ? sizeof(SW) : 0)),
           (double)n * 8 * nv * ((hu ? 1 : 0) + (hw ? 1 : 0)));
-  if (hw) {
-    KTimer kr(DW_K_REDUCE, s);
-    hipLaunchKernelGGL(k_reduce, 1, kThreads, 0, s, (const s64*)partials, (int)G, 1, (s64*)nrm2, 1, 0, gate,
-                       (const int*)nullptr, 0, 0);
-    DW_CHECK_LAUNCH();
-    kr.done((double)G * 16, 0);
-  }
   return DW_OK;
 }
 
-dw_status gs_update(int prec_v, void* V, long long stride, int nv, int jcol, const void* w, void* wout,
-                    const double* coef, long long n, double* partials, double* nrm2, hipStream_t s, const int* gate,
-                    const int* dcol, int prec_w) {
-  if (nv < 0 || nv > kMaxM + 1 || (jcol < 0 && !w && !dcol) || (prec_v != DW_PREC_F64 && prec_v != DW_PREC_F32) ||
-      (prec_w == DW_PREC_F32 && prec_v != DW_PREC_F32) || (prec_w != DW_PREC_F64 && prec_w != DW_PREC_F32)) {
+dw_status gs_update(int prec_v, void* V, long long stride, int nv, int jcol, int jw, const void* w, void* wout,
+                    const double* red, double* H, long long n, double* partials, int* nparts, hipStream_t s,
+                    const int* gate, const int* dcol, int prec_w) {
+  if (nv < 0 || nv > kMaxM + 1 || (jcol < 0 && !w && !dcol) || (w && (jw < 0 || jw >= kMaxM)) ||
+      (prec_v != DW_PREC_F64 && prec_v != DW_PREC_F32) || (prec_w == DW_PREC_F32 && prec_v != DW_PREC_F32) ||
+      (prec_w != DW_PREC_F64 && prec_w != DW_PREC_F32)) {
     set_error("gs_update: bad arguments");
     return DW_EINVAL;
   }
+  if (nparts) *nparts = (int)grid_for(n);
   if (prec_w == DW_PREC_F32)
-    return gs_update_t<s32, s32, float>((s32*)V, stride, nv, jcol, (const s32*)w, (s32*)wout, coef, n, partials,
-                                        nrm2, s, gate, dcol);
+    return gs_update_t<s32, s32, float>((s32*)V, stride, nv, jcol, jw, (const s32*)w, (s32*)wout, red, H, n, partials,
+                                        s, gate, dcol);
   if (prec_v == DW_PREC_F64)
-    return gs_update_t<s64, s64, double>((s64*)V, stride, nv, jcol, (const s64*)w, (s64*)wout, coef, n, partials,
-                                         nrm2, s, gate, dcol);
-  return gs_update_t<s32, s64, double>((s32*)V, stride, nv, jcol, (const s64*)w, (s32*)wout, coef, n, partials,
-                                       nrm2, s, gate, dcol);
+    return gs_update_t<s64, s64, double>((s64*)V, stride, nv, jcol, jw, (const s64*)w, (s64*)wout, red, H, n, partials,
+                                         s, gate, dcol);
+  return gs_update_t<s32, s64, double>((s32*)V, stride, nv, jcol, jw, (const s64*)w, (s32*)wout, red, H, n, partials, s,
+                                       gate, dcol);
 }
 
 }  // namespace dw

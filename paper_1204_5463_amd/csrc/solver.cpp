@@ -87,7 +87,7 @@ struct Shape {
 struct Work {
   int nr = 0, m = 0, k = 0;
   long long n = 0;
-  DevBuf V, Z, zs, w, r, x, b, vs, partials, H, c, eta, red, coef, nrm, Q, ritz, scal, proj, inj, zeta, ctl, ctld, mass;
+  DevBuf V, Z, zs, w, r, x, b, vs, partials, H, c, eta, red, nrm, Q, ritz, scal, proj, inj, zeta, ctl, ctld, mass;
   int* ctl_h = nullptr;
   double* ctld_h = nullptr;
   std::vector<std::unique_ptr<Shape>> shapes;
@@ -114,7 +114,6 @@ struct Work {
   double* cr(int r) const { return c.as<double>() + 2 * (long long)r * kLd; }
   double* etar(int r) const { return eta.as<double>() + 2 * (long long)r * kMaxM; }
   double* redr(int r) const { return red.as<double>() + 2 * (long long)r * (2 * kLd + 6); }
-  double* coefr(int r) const { return coef.as<double>() + 2 * (long long)r * (2 * kLd + 4); }
   double* nrmr(int r) const { return nrm.as<double>() + 2 * (long long)r; }
   double* Qr(int r) const { return Q.as<double>() + 2 * (long long)r * kLd * 25; }
   double* ritzr(int r) const { return ritz.as<double>() + 2 * (long long)r * kMaxM; }
@@ -175,7 +174,6 @@ dw_status alloc_work(dw_field f, const fgmresdr_params* P, int nr, Work& W, hipS
   DW_TRY(W.c.alloc(ctx, (size_t)nr * kLd * 16, s));
   DW_TRY(W.eta.alloc(ctx, (size_t)nr * kMaxM * 16, s));
   DW_TRY(W.red.alloc(ctx, (size_t)nr * (2 * kLd + 6) * 16, s));
-  DW_TRY(W.coef.alloc(ctx, (size_t)nr * (2 * kLd + 4) * 16, s));
   DW_TRY(W.nrm.alloc(ctx, (size_t)nr * 16, s));
   DW_TRY(W.Q.alloc(ctx, (size_t)nr * kLd * 25 * 16, s));
   DW_TRY(W.ritz.alloc(ctx, (size_t)nr * kMaxM * 16, s));
@@ -341,11 +339,11 @@ struct Solver {
         const int nv = lagged ? j : j + 1;
         DW_TRY(gs_reduce(W.vprec, V, n, nv, lagged ? W.Vc(r, j) : nullptr, W.wr(r), n, W.partr(r), W.redr(r), s,
                          gl, nullptr, wprec));
-        DW_TRY(dense_gs_coef(W.Hr(r), nv, lagged ? j : -1, j, lagged ? 1 : 0, 1, W.redr(r), W.coefr(r), W.scalr(r),
-                             kBdTol, s, gl));
-        DW_TRY(gs_update(W.vprec, V, n, nv, lagged ? j : -1, W.wr(r), W.Vc(r, j + 1), W.coefr(r), n, W.partr(r),
-                         W.nrmr(r), s, gl, nullptr, wprec));
-        DW_TRY(dense_step2(W.Hr(r), j, W.nrmr(r), W.cr(r), W.scalr(r), kBdTol, s, W.ctlr(r), W.ctldr(r)));
+        int nparts = 0;
+        DW_TRY(gs_update(W.vprec, V, n, nv, lagged ? j : -1, j, W.wr(r), W.Vc(r, j + 1), W.redr(r), W.Hr(r), n,
+                         W.partr(r), &nparts, s, gl, nullptr, wprec));
+        DW_TRY(dense_step2(W.Hr(r), j, j0_of(r), W.partr(r), nparts, W.cr(r), W.scalr(r), kBdTol, s, W.Qr(r),
+                           W.ctlr(r), W.ctldr(r)));
       }
     }
 
@@ -359,11 +357,10 @@ struct Solver {
       void* V = W.Vr(r);
       ProfTag tag_fin(kTagFin, 1ull << r);
       DW_TRY(gs_reduce(W.vprec, V, n, m, nullptr, nullptr, n, W.partr(r), W.redr(r), s, gfin, jend, wprec));
-      DW_TRY(dense_gs_coef(W.Hr(r), m, m, -1, 1, 0, W.redr(r), W.coefr(r), W.scalr(r), kBdTol, s, gfin, jend));
-      DW_TRY(gs_update(W.vprec, V, n, m, m, nullptr, nullptr, W.coefr(r), n, W.partr(r), nullptr, s, gfin, jend,
-                       wprec));
+      DW_TRY(gs_update(W.vprec, V, n, m, m, -1, nullptr, nullptr, W.redr(r), W.Hr(r), n, W.partr(r), nullptr, s,
+                       gfin, jend, wprec));
       ProfTag tag_cyc(kTagCycle, 1ull << r);
-      DW_TRY(dense_lsq(W.Hr(r), m, W.cr(r), W.etar(r), W.scalr(r), s, gcyc, jend));
+      DW_TRY(dense_lsq(W.Hr(r), m, W.cr(r), W.etar(r), W.scalr(r), s, gcyc, jend, W.Qr(r), W.gate(r, kCJ0)));
       DW_TRY(blas_combine(W.zstore, W.Zr(r), n, m, W.etar(r), 1.0, W.vec(W.x, r), n, s, gcyc, jend));
     }
     const int* rl_end = sh.rl.as<int>() + (size_t)m * nr;
