@@ -200,14 +200,16 @@ dw_status launch_pack_spinor(const Geom& g, int prec, const double* in, void* ou
                              hipStream_t s, const double* dscale = nullptr, int dstride = 0);
 dw_status launch_unpack_spinor(const Geom& g, int prec, const void* in, double* out, double scale, int nrhs,
                                hipStream_t s, const double* dscale = nullptr, int dstride = 0);
-dw_status launch_pack_gauge(const Geom& g, int prec, const double* in, void* out, hipStream_t s);
+// links at the four storage precisions (out[dw_prec]) from the canonical field
+dw_status launch_pack_gauge(const Geom& g, const double* in, void* const out[4], hipStream_t s);
 // sigma_{mu nu} chirality blocks (2x2) for the six planes mu < nu
 struct SigmaBlocks {
   double re[6][2][4], im[6][2][4];
 };
 SigmaBlocks sigma_blocks();
-// clover term (FP64, packed per dw_clover.hpp) from the FP64 internal links
-dw_status launch_clover_build(const Geom& g, const void* U64, double csw, double* out, hipStream_t s);
+// clover term (packed per dw_clover.hpp) at the four storage precisions
+// (out[dw_prec]) from the FP64 internal links
+dw_status launch_clover_build(const Geom& g, const void* U64, double csw, void* const out[4], hipStream_t s);
 // elementwise out = scale * (dscale ? dscale[0] : 1) * in over n pairs
 // (precision conversion; dscale is a device scalar)
 dw_status launch_convert(int pin, const void* in, int pout, void* out, double scale, long long n, hipStream_t s,

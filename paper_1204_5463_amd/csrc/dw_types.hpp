@@ -121,6 +121,9 @@ __host__ __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
 
 // round to nearest even; NaN stays NaN
 __host__ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_bit_cast(uint16_t, (__bf16)f);  // one conversion instruction
+#endif
   uint32_t u;
   __builtin_memcpy(&u, &f, 4);
   if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);

@@ -183,12 +183,12 @@ dw_status dw_field_create(dw_ctx ctx, const int32_t L[4], const int32_t block[4]
       set_error("dw_field_create: allocation of %zu bytes failed", bytes);
       return DW_ENOMEM;
     }
-    dw_status st = launch_pack_gauge(g, p, U_dev, f->U[p], stream);
-    if (st != DW_OK) {
-      for (int q = 0; q <= p; ++q) dev_free(ctx, f->U[q], stream);
-      delete f;
-      return st;
-    }
+  }
+  const dw_status st = launch_pack_gauge(g, U_dev, f->U, stream);
+  if (st != DW_OK) {
+    for (int q = 0; q < 4; ++q) dev_free(ctx, f->U[q], stream);
+    delete f;
+    return st;
   }
   ctx->refs.fetch_add(1);
   *out = f;
@@ -244,9 +244,7 @@ dw_status dw_field_set_clover(dw_field f, double csw, hipStream_t stream) {
       return DW_ENOMEM;
     }
   }
-  DW_TRY(launch_clover_build(f->g, f->U[DW_PREC_F64], csw, (double*)f->C[DW_PREC_F64], stream));
-  for (int p = 1; p < 4; ++p) DW_TRY(launch_convert(DW_PREC_F64, f->C[DW_PREC_F64], p, f->C[p], 1.0, n, stream));
-  return DW_OK;
+  return launch_clover_build(f->g, f->U[DW_PREC_F64], csw, f->C, stream);
 }
 
 int64_t dw_field_volume(dw_field f) { return f ? (int64_t)f->g.V : 0; }
@@ -264,13 +262,9 @@ dw_status field_reload(dw_field f, const double* U_dev, double csw, hipStream_t 
     return DW_EINVAL;
   }
   DW_TRY(check_device(f->ctx));
-  for (int p = 0; p < 4; ++p) DW_TRY(launch_pack_gauge(f->g, p, U_dev, f->U[p], stream));
+  DW_TRY(launch_pack_gauge(f->g, U_dev, f->U, stream));
   f->csw = csw;
-  if (csw != 0.0) {
-    const long long n = f->g.V * kCloverPairs;
-    DW_TRY(launch_clover_build(f->g, f->U[DW_PREC_F64], csw, (double*)f->C[DW_PREC_F64], stream));
-    for (int p = 1; p < 4; ++p) DW_TRY(launch_convert(DW_PREC_F64, f->C[DW_PREC_F64], p, f->C[p], 1.0, n, stream));
-  }
+  if (csw != 0.0) DW_TRY(launch_clover_build(f->g, f->U[DW_PREC_F64], csw, f->C, stream));
   return DW_OK;
 }
 
