@@ -42,8 +42,8 @@ __device__ __forceinline__ void clover_acc(const SC* __restrict__ Cb, int bvol, 
 #pragma unroll
       for (int j = i + 1; j < 6; ++j) {
         const cplx<T> o = ld<T>(c + (q++) * bvol);
-        w[i] += o * v[j];
-        w[j] += cdot(o, v[i]);
+        cmac(w[i], o, v[j]);
+        cmacj(w[j], o, v[i]);
       }
 #pragma unroll
     for (int i = 0; i < 6; ++i) y[6 * chi + i] += w[i];
@@ -66,8 +66,8 @@ __device__ __forceinline__ void clover_chi(const SC* __restrict__ c, int stride,
 #pragma unroll
     for (int j = i + 1; j < 6; ++j) {
       const cplx<T> o = ld<T>(c + (q++) * stride);
-      w[i] += o * v[j];
-      w[j] += cdot(o, v[i]);
+      cmac(w[i], o, v[j]);
+      cmacj(w[j], o, v[i]);
     }
 }
 
@@ -94,8 +94,8 @@ __device__ __forceinline__ void clover_acc_f(const SC* __restrict__ Cb, int bvol
 #pragma unroll
       for (int j = i + 1; j < 6; ++j) {
         const cplx<T> o = ld<T>(c + (q++) * bvol);
-        w[i] += o * v[j];
-        w[j] += cdot(o, v[i]);
+        cmac(w[i], o, v[j]);
+        cmacj(w[j], o, v[i]);
       }
 #pragma unroll
     for (int i = 0; i < 6; ++i) y[6 * chi + i] += s * w[i];

@@ -45,7 +45,7 @@ constexpr int kWave = 64;
 // Wavefront sum. FP32: an inclusive scan within each row of 16 lanes by
 // DPP row shifts, then the row totals combined by the row broadcasts, so
 // that lane 63 holds the sum (no LDS traffic); its value is returned to all
-// lanes. FP64 goes through cross-lane shuffles.
+// lanes. FP64 the same on register pairs.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ float dpp_add(float v) {
   const int s = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false);
@@ -62,10 +62,23 @@ __device__ __forceinline__ T wave_sum(T a) {
     a = dpp_add<0x143, 0xc>(a);  // row_bcast:31 into rows 2 and 3
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 63));
   } else {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) a += __shfl_xor(a, off, kWave);
-    return a;
+    return wave_total(a);
   }
+}
+
+// Algorithmic traffic per site of one colour: v, 4 links, z read (or the other
+// colour's z cleared) and z written; flops: block residual stencil plus nmr MR
+// steps (block stencil over the kept hops + 4 block vector ops); with the
+// adaptive stop nmr is only the cap and the flops an upper bound
+template <typename SV, typename SZ, typename SG, bool CLOV>
+void sap_done(KTimer& kt, const Geom& g, int nmr, int z_zero, int nrhs) {
+  double kept = 0;
+  for (int mu = 0; mu < 4; ++mu) kept += 2.0 * (g.B[mu] - 1) / g.B[mu];
+  const double sites = (double)g.nbc * g.bvol * nrhs;
+  const double sv = sizeof(SV), sz = sizeof(SZ), sg = sizeof(SG);
+  const double csteps = CLOV ? nmr + (z_zero ? 0 : 1) : 0;
+  kt.done(sites * (12 * sv + 36 * sg + 24 * sz + (CLOV ? kCloverPairs * sg : 0)),
+          sites * ((z_zero ? 0.0 : 1368.0) + nmr * (48.0 + 168.0 * kept + 336.0) + csteps * kCloverFlops));
 }
 
 // BS > 0: hypercubic BS^4 blocks known at compile time (LDS offsets and
@@ -370,17 +383,7 @@ dw_status launch_t(const Geom& g, double m0, const void* v, void* z, const void*
                      (T)(4.0 + m0), (const SV*)v, (SZ*)z, (const SG*)U, nmr, z_zero, vs, zs, nrhs, rlist,
                      (const SG*)C, (T)red2, gate, gs, dmass);
   DW_CHECK_LAUNCH();
-  // algorithmic traffic per site of this colour: v, 4 links, z read (or the
-  // other colour's z cleared) and z written; flops: block residual stencil
-  // plus nmr MR steps (block stencil over the kept hops + 4 block vector ops);
-  // with the adaptive stop nmr is only the cap and the flops an upper bound
-  double kept = 0;
-  for (int mu = 0; mu < 4; ++mu) kept += 2.0 * (g.B[mu] - 1) / g.B[mu];
-  const double sites = (double)g.nbc * g.bvol * nrhs;
-  const double sv = sizeof(SV), sz = sizeof(SZ), sg = sizeof(SG);
-  const double csteps = CLOV ? nmr + (z_zero ? 0 : 1) : 0;
-  kt.done(sites * (12 * sv + 36 * sg + 24 * sz + (CLOV ? kCloverPairs * sg : 0)),
-          sites * ((z_zero ? 0.0 : 1368.0) + nmr * (48.0 + 168.0 * kept + 336.0) + csteps * kCloverFlops));
+  sap_done<SV, SZ, SG, CLOV>(kt, g, nmr, z_zero, nrhs);
   return DW_OK;
 }
 
@@ -394,7 +397,7 @@ dw_status launch_m(const Geom& g, double m0, const void* v, void* z, const void*
   // with FP16 links: 380 us with links from L1/L2, 517 us staged).
   const size_t need = (size_t)36 * g.bvol * sizeof(SG) + (size_t)12 * g.bvol * sizeof(cplx<T>) + 512;
   const bool hyper4 = g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4;
-  if constexpr (MAXT == 256)
+  if constexpr (MAXT == 256 && is_link16<SG>)  // the other storages of 4^4 blocks are taken by launch_split
     if (hyper4 && need > 40 * 1024)
       return launch_t<T, SV, SZ, SG, 256, false, 4, CLOV>(g, m0, v, z, U, colour, nmr, z_zero, nrhs, vs, zs, rlist, s,
                                                           C, red2, gate, gs, dmass);
@@ -405,10 +408,24 @@ dw_status launch_m(const Geom& g, double m0, const void* v, void* z, const void*
                                                        C, red2, gate, gs, dmass);
 }
 
+}  // namespace sapk
+
+}  // namespace dw
+
+#include "dw_sap_split.hpp"
+
+namespace dw {
+
+namespace sapk {
+
 template <typename T, typename SV, typename SZ, typename SG, bool CLOV>
 dw_status launch_b(const Geom& g, double m0, const void* v, void* z, const void* U, int colour, int nmr, int z_zero,
                    int nrhs, long long vs, long long zs, const int* rlist, hipStream_t s, const void* C,
                    double red2, const int* gate, int gs, const double* dmass) {
+  if constexpr (!is_link16<SG>)
+    if (g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4)
+      return launch_split<T, SV, SZ, SG, CLOV>(g, m0, v, z, U, colour, nmr, z_zero, nrhs, vs, zs, rlist, s, C, red2,
+                                               gate, gs, dmass);
   if (g.bvol <= 256)
     return launch_m<T, SV, SZ, SG, 256, CLOV>(g, m0, v, z, U, colour, nmr, z_zero, nrhs, vs, zs, rlist, s, C, red2, gate, gs, dmass);
   if (g.bvol <= 512)

@@ -51,6 +51,14 @@ __host__ __device__ __forceinline__ void cmac(cplx<T>& acc, cplx<T> a, cplx<T> b
   acc.im = fma(a.re, b.im, acc.im);
   acc.im = fma(a.im, b.re, acc.im);
 }
+// acc += conj(a) b
+template <typename T>
+__host__ __device__ __forceinline__ void cmacj(cplx<T>& acc, cplx<T> a, cplx<T> b) {
+  acc.re = fma(a.re, b.re, acc.re);
+  acc.re = fma(a.im, b.im, acc.re);
+  acc.im = fma(a.re, b.im, acc.im);
+  acc.im = fma(-a.im, b.re, acc.im);
+}
 template <typename T>
 __host__ __device__ __forceinline__ void cmsub(cplx<T>& acc, cplx<T> a, cplx<T> b) {
   acc.re = fma(-a.re, b.re, acc.re);
