@@ -194,8 +194,8 @@ __global__ void __launch_bounds__(kThreads)
 template <bool HU, bool HW, typename SV, typename SW, typename T>
 __global__ void __launch_bounds__(kThreads)
     k_gs_reduce(const SV* __restrict__ V, long long stride, int nv, const SV* __restrict__ u,
-                const SW* __restrict__ w, long long n, s64* __restrict__ partials, const int* __restrict__ gate,
-                const int* __restrict__ dcol) {
+                const SW* __restrict__ w, long long n, int nch, s64* __restrict__ partials,
+                const int* __restrict__ gate, const int* __restrict__ dcol) {
   constexpr int NA = kGsCols;
   if (gate && *gate == 0) return;
   if (dcol) {
@@ -203,9 +203,16 @@ __global__ void __launch_bounds__(kThreads)
     nv = *dcol;
     u = V + (long long)nv * stride;
   }
-  // the columns in chunks of at most NA, split evenly, one chunk per grid row
-  // (each chunk reads u and w again)
-  const int chunk = blockIdx.y;
+  // The columns in chunks of at most NA, split evenly, one workgroup per chunk
+  // and range of elements (each chunk reads u and w again). The nch workgroups of
+  // a range follow each other on one XCD, so that u and w come from its L2 and
+  // the sweep moves through the elements with all columns: the update sweep,
+  // which goes back, finds what was read last in the memory-side cache.
+  const int G = gridDim.x / nch;
+  const bool by_xcd = G % kXcds == 0;
+  const int kk = by_xcd ? blockIdx.x / kXcds : blockIdx.x;
+  const int chunk = kk % nch;
+  const int bx = by_xcd ? kk / nch * kXcds + blockIdx.x % kXcds : kk / nch;
   const int nchunks = nv > 0 ? (nv + NA - 1) / NA : 1;
   if (chunk >= nchunks) return;
   const int per = nv > 0 ? (nv + nchunks - 1) / nchunks : 0;
@@ -219,8 +226,8 @@ __global__ void __launch_bounds__(kThreads)
     au[c] = mk<T>(0, 0);
     aw[c] = mk<T>(0, 0);
   }
-  const long long step = (long long)gridDim.x * kThreads;
-  for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n; i += step) {
+  const long long step = (long long)G * kThreads;
+  for (long long i = (long long)bx * kThreads + threadIdx.x; i < n; i += step) {
     cplx<T> uv = mk<T>(0, 0), wv = mk<T>(0, 0);
     if constexpr (HU) uv = ld<T>(u + i);
     if constexpr (HW) wv = ld<T>(w + i);
@@ -254,7 +261,6 @@ __global__ void __launch_bounds__(kThreads)
   put(2 * NA + 1, uw);
   put(2 * NA + 2, ww);
   __syncthreads();
-  const int G = gridDim.x;
   for (int t = threadIdx.x; t < 2 * NA + 3; t += kThreads) {
     int slot;
     if (t < NA) {
@@ -272,7 +278,7 @@ __global__ void __launch_bounds__(kThreads)
       re += red[q][t][0];
       im += red[q][t][1];
     }
-    partials[(long long)slot * G + blockIdx.x] = s64{re, im};
+    partials[(long long)slot * G + bx] = s64{re, im};
   }
 }
 
@@ -337,7 +343,12 @@ __global__ void __launch_bounds__(kThreads)
   __syncthreads();
   double nrm = 0;
   const long long step = (long long)gridDim.x * kThreads;
-  for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n; i += step) {
+  // from the last elements to the first: the reduction sweep before went the
+  // other way, so what it read last is still in the memory-side cache
+  const long long rounds = (n + step - 1) / step;
+  for (long long q = rounds - 1; q >= 0; --q) {
+    const long long i = q * step + (long long)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n) continue;
     cplx<T> uu = mk<T>(0, 0), wa = mk<T>(0, 0);
     if constexpr (HU) uu = ld<T>(V + (long long)jcol * stride + i);
     if constexpr (HW) wa = ld<T>(w + i);
@@ -474,18 +485,18 @@ dw_status gs_reduce_t(const SV* Vp, long long stride, int nv, const SV* up, cons
   const bool hu = up != nullptr || dcol != nullptr, hw = wp != nullptr;
   const unsigned G = grid_for(n);
   const int nchunks = nv > 0 ? (nv + kGsCols - 1) / kGsCols : 1;  // with dcol nv bounds the device's count
-  const dim3 grid(G, (unsigned)nchunks);
+  const unsigned grid = G * (unsigned)nchunks;
   KTimer kt(DW_K_DOTS, s);
   s64* part = (s64*)partials;
   if (hu && hw)
-    hipLaunchKernelGGL((k_gs_reduce<true, true, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, part, gate,
-                       dcol);
+    hipLaunchKernelGGL((k_gs_reduce<true, true, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, nchunks, part,
+                       gate, dcol);
   else if (hu)
-    hipLaunchKernelGGL((k_gs_reduce<true, false, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, part, gate,
-                       dcol);
+    hipLaunchKernelGGL((k_gs_reduce<true, false, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, nchunks, part,
+                       gate, dcol);
   else
-    hipLaunchKernelGGL((k_gs_reduce<false, true, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, part, gate,
-                       dcol);
+    hipLaunchKernelGGL((k_gs_reduce<false, true, SV, SW, T>), grid, kThreads, 0, s, Vp, stride, nv, up, wp, n, nchunks, part,
+                       gate, dcol);
   DW_CHECK_LAUNCH();
   kt.done((double)n * (sizeof(SV) * (nv + (hu ? 1 : 0)) + (hw ? sizeof(SW) : 0)),
           (double)n * 8 * nv * ((hu ? 1 : 0) + (hw ? 1 : 0)));
