@@ -17,8 +17,8 @@
 // CANON: x, y and b in the canonical layout (12 contiguous complex numbers per
 // site), so that an application on caller fields needs no packing pass: packing,
 // the operator on the internal layout and unpacking moved 2.7 times the bytes
-// (32^3x64, 12 right-hand sides: 8931 -> 5330 us per application; 8^4: 22.5 ->
-// 13.5 us, one launch for three and no allocation).
+// (32^3x64, 12 right-hand sides: 8931 -> 5260 us per application; 8^4: 22.5 ->
+// 12.0 us, one launch for three and no allocation).
 //
 // Bound: memory. At 12 right-hand sides the launch moves about 0.8 KB per site
 // and right-hand side beyond the L2 (spinor in and out, faces, links shared).
@@ -96,12 +96,16 @@ __device__ __forceinline__ cplx<T> face(const Ctx<T, SX, SG>& c, int nb, int nl,
   else return ld<T>(c.xr + spinor_index(c.g, nb, k, nl));
 }
 
-template <int MU, bool CANON, typename T, typename SX, typename SG>
+template <int MU, bool CANON, int BS, typename T, typename SX, typename SG>
 __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx<T> low[3]) {
   constexpr bool IM = kImag<MU>;
   const Geom& g = c.g;
-  const int bvol = g.bvol, l = c.l, r = c.r;
-  const int st = g.lstride[MU];
+  // x and y on 4^4 blocks: a row of 16 lanes is an x-y plane, so the products go
+  // to the neighbour by a lane shift, without LDS and barriers
+  constexpr bool SHIFT = BS == 4 && MU < 2;
+  const int bvol = BS ? BS * BS * BS * BS : g.bvol, l = c.l, r = c.r;
+  const int bm = BS ? BS : g.B[MU];
+  const int st = BS ? (MU == 0 ? 1 : MU == 1 ? BS : MU == 2 ? BS * BS : BS * BS * BS) : g.lstride[MU];
   // alpha of the forward hop is sg (times i for x and z): +i, +-1, +-i, -1
   const T sg = MU == 0 ? (T)1 : MU == 3 ? (T)-1 : c.rs;
   const int ks = 3 * r, kp = MU < 2 ? 9 - 3 * r : 6 + 3 * r;
@@ -110,7 +114,7 @@ __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx
 #pragma unroll
     for (int d = 0; d < MU; ++d) cst *= g.L[d];
   }
-  cplx<T> h[3], v[3];
+  cplx<T> h[3], v[3], handed[3];
   if (c.active) {
     cplx<T> w[9];
 #pragma unroll
@@ -120,10 +124,16 @@ __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx
     for (int a = 0; a < 3; ++a)
       h[a] = proj1<IM, T>(ld<T>(c.xsh + (ks + a) * bvol + l), -sg, ld<T>(c.xsh + (kp + a) * bvol + l));
     mul1<true, T>(w, h, v);
+    if constexpr (SHIFT) {
+      // 256 sites: every lane is active
 #pragma unroll
-    for (int a = 0; a < 3; ++a) c.pb[(ks + a) * bvol + l] = v[a];
+      for (int a = 0; a < 3; ++a) handed[a] = lane_shift<MU, -1>(v[a]);
+    } else {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) c.pb[(ks + a) * bvol + l] = v[a];
+    }
     // forward hop (1 - g_mu) U_mu(n) psi(n + mu)
-    if (c.lc[MU] < g.B[MU] - 1) {
+    if (c.lc[MU] < bm - 1) {
 #pragma unroll
       for (int a = 0; a < 3; ++a)
         h[a] = proj1<IM, T>(ld<T>(c.xsh + (ks + a) * bvol + l + st), sg, ld<T>(c.xsh + (kp + a) * bvol + l + st));
@@ -138,7 +148,7 @@ __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx
         c2[MU] = wrap ? 0 : c.bc[MU] + 1;
         nb = encode_block(g, c2);
       }
-      const int nl = l - (g.B[MU] - 1) * st;
+      const int nl = l - (bm - 1) * st;
 #pragma unroll
       for (int a = 0; a < 3; ++a)
         h[a] = proj1<IM, T>(face<CANON>(c, nb, nl, nn, ks + a), sg, face<CANON>(c, nb, nl, nn, kp + a));
@@ -150,16 +160,16 @@ __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx
       rec1<IM, T>(low[a], sg, v[a]);
     }
   }
-  __syncthreads();
+  if constexpr (!SHIFT) __syncthreads();
   if (c.active) {
     if (c.lc[MU] > 0) {
 #pragma unroll
-      for (int a = 0; a < 3; ++a) v[a] = c.pb[(ks + a) * bvol + l - st];
+      for (int a = 0; a < 3; ++a) v[a] = SHIFT ? handed[a] : c.pb[(ks + a) * bvol + l - st];
     } else {
       const bool wrap = c.bc[MU] == 0;
       int c2[4] = {c.bc[0], c.bc[1], c.bc[2], c.bc[3]};
       c2[MU] = wrap ? g.N[MU] - 1 : c.bc[MU] - 1;
-      const int nb = encode_block(g, c2), nl = l + (g.B[MU] - 1) * st;
+      const int nb = encode_block(g, c2), nl = l + (bm - 1) * st;
       const long long nn = CANON ? c.n + (wrap ? cst * ((long long)g.L[MU] - 1) : -cst) : 0;
 #pragma unroll
       for (int a = 0; a < 3; ++a)
@@ -175,7 +185,7 @@ __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx
       rec1<IM, T>(low[a], -sg, v[a]);
     }
   }
-  if constexpr (MU < 3) __syncthreads();
+  if constexpr (MU < 3 && !SHIFT) __syncthreads();
 }
 
 }  // namespace rows
@@ -197,9 +207,25 @@ size_t rows_lds(const Geom& g) {
 template <typename T, typename SX>
 bool rows_fits(const Geom& g) { return rows_threads(g) <= 1024 && rows_lds<T, SX>(g) <= 160 * 1024; }
 
+// 4^4 blocks, at most one workgroup per CU: a launch is one chain of loads and
+// barriers, which the BS = 4 form shortens (8^4, dw_apply: 13.5 -> 12.0 us, 192
+// workgroups 17.2 -> 15.7, 256: 21.1 -> 19.1). From the second workgroup per CU on
+// its registers cost more than the latency gives (384: 26.1 -> 28.9 us, 512: 34.0 ->
+// 34.4, 6144: 320 -> 383). The two forms do the same arithmetic, bit for bit.
+inline bool rows_alone(const Geom& g, int nrhs) {
+  constexpr int kCUs = 256;
+  return g.nblk * nrhs <= kCUs && g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4;
+}
+
 // MODE 0: y = scale * D x; MODE 1: y = b - scale * D x
-template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV, bool CANON>
-__global__ void __launch_bounds__(1024)
+// MAXT: largest workgroup of the instantiation, 1024 for blocks above 256 sites.
+// Promising 512 where that holds lets the compiler order the loads for the four
+// waves a SIMD has registers for (32^3 x 64, 12 sides: 5525 -> 5260 us).
+// BS: 4 for 4^4 blocks known at compile time, else 0. With the strides constant
+// the compiler has all loads of a site in flight at once, at 148 to 188 registers:
+// two waves per SIMD. rows_alone() says where that is the better trade.
+template <typename T, typename SX, typename SG, typename SY, int MODE, int MAXT, int BS, bool CLOV, bool CANON>
+__global__ void __launch_bounds__(MAXT)
     k_dslash_rows(Geom g, T diag, const SX* __restrict__ x, T scale, const SG* __restrict__ U, SY* __restrict__ y,
                   const SY* __restrict__ bsrc, long long xs, long long ys, int nr, const int* __restrict__ rlist,
                   const SG* __restrict__ Cl, DCtl dc) {
@@ -207,7 +233,9 @@ __global__ void __launch_bounds__(1024)
   SX* xsh = reinterpret_cast<SX*>(smem);
   cplx<T>* pb = reinterpret_cast<cplx<T>*>(smem + (((size_t)12 * g.bvol * sizeof(SX) + 15) & ~(size_t)15));
   // work item -> (block, RHS) with the RHS fastest: workgroups that read the
-  // same links run together on one XCD
+  // same links run together on one XCD. (Two right-hand sides at a time, for
+  // all blocks: 5 x 3 x 3 x 5 blocks 57.6 -> 52.5 us, but 16^3 x 8, 12 sides,
+  // 76 -> 80 us and 32^3 x 64 5260 -> 5345 us.)
   const int wi = xcd_remap(blockIdx.x, g.nblk * nr);
   if (wi < 0) return;  // uniform for the workgroup
   const int b = wi / nr;
@@ -240,10 +268,10 @@ __global__ void __launch_bounds__(1024)
   cplx<T> up[3], lowxy[3], lowzt[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) up[a] = lowxy[a] = lowzt[a] = mk<T>(0, 0);
-  rows::dir<0, CANON>(c, up, lowxy);
-  rows::dir<1, CANON>(c, up, lowxy);
-  rows::dir<2, CANON>(c, up, lowzt);
-  rows::dir<3, CANON>(c, up, lowzt);
+  rows::dir<0, CANON, BS>(c, up, lowxy);
+  rows::dir<1, CANON, BS>(c, up, lowxy);
+  rows::dir<2, CANON, BS>(c, up, lowzt);
+  rows::dir<3, CANON, BS>(c, up, lowzt);
   // spin 2 + r: this lane's z/t sum and the other lane's x/y sum
 #pragma unroll
   for (int a = 0; a < 3; ++a) lowzt[a] += rows::other_row(lowxy[a]);

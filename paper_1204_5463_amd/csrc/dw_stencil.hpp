@@ -471,6 +471,24 @@ __device__ __forceinline__ W lane_below(W v) {
   }
 }
 
+// On 4^4 blocks a row of 16 lanes is an x-y plane of the block. Value of lane + 1
+// (MU 0) or lane + 4 (MU 1) for DIR > 0, lane - 1 or - 4 for DIR < 0: the
+// neighbour site's. 0 from outside the row, another row of the plane at the x faces.
+template <int MU, int DIR>
+__device__ __forceinline__ float lane_shift(float v) {
+  constexpr int ctrl = (DIR > 0 ? 0x100 : 0x110) + (MU == 0 ? 1 : 4);  // row_shl, row_shr
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
+}
+template <int MU, int DIR>
+__device__ __forceinline__ double lane_shift(double v) {
+  constexpr int ctrl = (DIR > 0 ? 0x100 : 0x110) + (MU == 0 ? 1 : 4);
+  return dpp64<ctrl, 0xf, true>(0.0, v);
+}
+template <int MU, int DIR, typename T>
+__device__ __forceinline__ cplx<T> lane_shift(cplx<T> v) {
+  return mk<T>(lane_shift<MU, DIR>(v.re), lane_shift<MU, DIR>(v.im));
+}
+
 // One direction of hop_sum_block_unrolled (below). Directions MU < NREG take
 // their links from registers (ux[MU], the lane's own site's links, held across
 // calls): the forward hop uses them directly and the backward hop those of the

@@ -321,7 +321,9 @@ dw_status launch_rows(const Geom& g, T diag, const SX* x, T scale, const SG* U, 
     DW_CHECK_LAUNCH();
     return DW_OK;
   };
-  return go(k_dslash_rows<T, SX, SG, SY, MODE, CLOV, CANON>);
+  if (rows_alone(g, nrhs)) return go(k_dslash_rows<T, SX, SG, SY, MODE, 512, 4, CLOV, CANON>);
+  if (threads <= 512) return go(k_dslash_rows<T, SX, SG, SY, MODE, 512, 0, CLOV, CANON>);
+  return go(k_dslash_rows<T, SX, SG, SY, MODE, 1024, 0, CLOV, CANON>);
 }
 
 template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV>

@@ -48,3 +48,35 @@ def test_fp64_operator_block_edges(dwctx, block, csw):
         assert np.max(np.abs(y[r] - ref)) <= 2e-14 * scale, (block, r)
         assert np.max(np.abs(ye[r] - ref)) <= 2e-14 * scale, (block, r)
     f.close()
+
+
+@pytest.mark.parametrize("csw", [0.0, 1.9])
+def test_fp64_operator_4x4x4x4_forms(dwctx, csw):
+    """4^4 blocks: 16 blocks x 16 right-hand sides is the largest launch of the
+    one-workgroup-per-CU form, 17 the smallest of the general one. The oracle
+    bound at the first and last right-hand side, and the same bits from both."""
+    L, block, m0 = (8, 8, 8, 8), (4, 4, 4, 4), -0.4
+    U = synth.gauge_field(L, 0.7, 5)
+    f = P.Field(dwctx, L, block, P.to_device(U))
+    C = None
+    if csw:
+        f.set_clover(csw)
+        C = Cl.clover_term(U, csw)
+    x = synth.gaussian_spinors(L, 17)
+    xt = P.to_device(x)
+    xi = f.pack(P.DW_PREC_F64, xt)
+    out = {}
+    for nr in (16, 17):
+        y = f.apply(m0, xt[:nr].contiguous())
+        yi = torch.empty_like(xi)
+        f.apply_ex(m0, P.DW_PREC_F64, xi, yi, nrhs=nr)
+        out[nr] = y.cpu(), f.unpack(P.DW_PREC_F64, yi, nrhs=nr).cpu()
+    for r in (0, 15):
+        ref = W.apply_D(U, m0, x[r])
+        if csw:
+            ref = ref + Cl.apply_clover(C, x[r])
+        for y in out[16]:
+            assert np.max(np.abs(y[r].numpy() - ref)) <= 2e-14 * np.max(np.abs(ref)), r
+    for a, b in zip(out[16], out[17]):
+        assert torch.equal(a, b[:16])
+    f.close()
