@@ -4,21 +4,26 @@
 // (i c_sw / 2) sum sigma^chi_{mu nu} (x) F_{mu nu}, stored packed at all four
 // precisions.
 //
-// Q enters only as Q - Q^+, so a leaf may be replaced by minus its conjugate,
-// and the four leaves group into
-//   Q' = [V A1 + W^+ A2] U^+ + [V B1 + W^+ B2] X,
-//   U = U_mu(n), X = U_mu(n-mu), V = U_nu(n), W = U_nu(n-nu),
-//   A1 = -U_mu(n+nu) U_nu(n+mu)^+,       A2 = U_mu(n-nu) U_nu(n+mu-nu),
-//   B1 = U_mu(n-mu+nu)^+ U_nu(n-mu)^+,   B2 = -U_mu(n-mu-nu)^+ U_nu(n-mu-nu):
-// 10 products and 14 link reads per plane instead of 12 and 16. A neighbour's
-// offset in the tiled layout is the sum of one term per direction, computed
-// once per site (the divisions of the index arithmetic, per link, were most of
-// the instructions). In the chiral basis the planes xy and zt fill the spin-
-// diagonal blocks and the other four the off-diagonal one, so the two groups
+// Q enters only as Q - Q^+, so a leaf may be replaced by minus its conjugate, and
+// the four leaves group into
+//   Q' = T(n) U_mu(n)^+ - T(n-mu)^+ U_mu(n-mu),
+//   T(n) = U_nu(n-nu)^+ U_mu(n-nu) U_nu(n+mu-nu) - U_nu(n) U_mu(n+nu) U_nu(n+mu)^+,
+// the difference of the two staples of U_mu(n). A site computes T(n) once (4
+// products, 6 link reads), its own term and, handed to site n+mu through LDS, the
+// other site's: 6 products and 7 link reads per plane. Only the Hermitian part is
+// handed over, 9 numbers. Where n-mu is outside the workgroup's 256 sites its T is
+// computed here as well, by a compact list of such sites (a quarter of them on 4^4
+// blocks, one wave per plane, a different one each time).
+// A neighbour's offset in the tiled layout is the sum of one term per direction,
+// computed once per site (the divisions of the index arithmetic, per link, were
+// most of the instructions). In the chiral basis the planes xy and zt fill the
+// spin-diagonal blocks and the other four the off-diagonal one, so the two groups
 // are accumulated and stored one after the other, which keeps the 42 entries
 // of a site out of the registers.
-// Bound by the L2: 12 KB of links per site at about 9.5 TB/s. 24^3x48: 886 us and
-// 285 us of conversions -> 840 us.
+// Bound by the link reads from the L2, at two waves per SIMD. 24^3x48: the four
+// leaves of each site by themselves, 10 products and 14 link reads per plane, 840 us
+// -> 647 us. (All sites of the lists at the start instead, spread over the waves:
+// 288 B of spills, 984 us.)
 #include "dw_clover.hpp"
 #include "dw_internal.hpp"
 
@@ -69,21 +74,29 @@ struct CloverOut {
   s32* o32;
   s16* o16;
   sbf* obf;
-  __device__ __forceinline__ void put(long long at, C v) const {
-    st(o64 + at, v);
-    st(o32 + at, v);
-    st(o16 + at, v);
-    st(obf + at, v);
+  __device__ __forceinline__ void put(long long at, C v, bool on) const {
+    if (on) {
+      st(o64 + at, v);
+      st(o32 + at, v);
+      st(o16 + at, v);
+      st(obf + at, v);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 };
 
 __global__ void __launch_bounds__(kThreads, 2)
     k_clover_build(Geom g, const s64* __restrict__ U, SigmaBlocks sb, double csw, CloverOut out) {
+  __shared__ double own[9][kThreads], far[9][kThreads];  // handed over; by the list, for its site
+  __shared__ long long hereL[kThreads], dnL[3][kThreads], upL[3][kThreads], dnN[3][kThreads];
+  __shared__ short list[3][kThreads];  // threads whose n - d is outside the workgroup
+  __shared__ int count[3];
   const int chunk = xcd_remap(blockIdx.x, (int)((g.V + kThreads - 1) / kThreads));
-  if (chunk < 0) return;
-  const long long s = (long long)chunk * kThreads + threadIdx.x;
-  if (s >= g.V) return;
+  if (chunk < 0) return;  // uniform for the workgroup
+  const int tid = threadIdx.x;
+  const long long s0 = (long long)chunk * kThreads;
+  const bool active = s0 + tid < g.V;
+  const long long s = active ? s0 + tid : g.V - 1;
   const int b = (int)(s / g.bvol);
   const int l = (int)(s - (long long)b * g.bvol);
   int bc[4], lc[4];
@@ -91,22 +104,37 @@ __global__ void __launch_bounds__(kThreads, 2)
   decode_local(g, l, lc);
   // offsets of the neighbours n + d and n - d
   long long up[4], dn[4];
-  long long bst = (long long)36 * g.bvol;
+  int before[3];  // thread of n - d, or -1
+  if (tid < 3) count[tid] = 0;
+  __syncthreads();
+  long long bst = g.bvol;
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
     const long long across = (long long)(g.B[d] - 1) * g.lstride[d], turn = (long long)(g.N[d] - 1) * bst;
-    up[d] = lc[d] < g.B[d] - 1 ? g.lstride[d] : (bc[d] < g.N[d] - 1 ? bst : -turn) - across;
-    dn[d] = lc[d] > 0 ? -g.lstride[d] : (bc[d] > 0 ? -bst : turn) + across;
+    const long long ub = bc[d] < g.N[d] - 1 ? bst : -turn, db = bc[d] > 0 ? -bst : turn;
+    up[d] = lc[d] < g.B[d] - 1 ? g.lstride[d] : 36 * ub - across;
+    dn[d] = lc[d] > 0 ? -g.lstride[d] : 36 * db + across;
+    if (d < 3) {
+      const long long at = s + (lc[d] > 0 ? -g.lstride[d] : db + across) - s0;
+      before[d] = at >= 0 && at < kThreads ? (int)at : -1;
+      if (active && before[d] < 0) list[d][atomicAdd(&count[d], 1)] = (short)tid;
+      dnL[d][tid] = dn[d];
+    }
+    if (d > 0) {
+      upL[d - 1][tid] = up[d];
+      dnN[d - 1][tid] = dn[d];
+    }
     bst *= g.N[d];
   }
-  const s64* here = U + (long long)b * 36 * g.bvol + l;
+  hereL[tid] = (long long)b * 36 * g.bvol + l;
+  __syncthreads();
   // entry reader of the link U_mu at offset ofs. The pointer goes through an
   // offset the compiler cannot see through: links that appear in two products
   // are read again from the L1 instead of being held
-  auto link = [&](int mu, long long ofs) {
+  auto link = [&](long long ofs, int mu) {
     int zero = 0;
     asm volatile("" : "+v"(zero));
-    const s64* p = here + ofs + (long long)mu * 9 * g.bvol + zero;
+    const s64* p = U + ofs + (long long)mu * 9 * g.bvol + zero;
     return [p, &g](int e) { return ld<double>(p + e * g.bvol); };
   };
   auto whole = [](auto&& f) {
@@ -115,31 +143,51 @@ __global__ void __launch_bounds__(kThreads, 2)
     for (int e = 0; e < 9; ++e) r.e[e] = f(e);
     return r;
   };
-  // f = (i csw / 2) F of plane (mu, nu), Hermitian: (i csw / 16) (Q' - Q'^+)
-  auto plane = [&](int mu, int nu) {
-    const long long pu = pick(up, mu), mm = pick(dn, mu), pv = pick(up, nu), mv = pick(dn, nu);
-    M3 q, t, r;
-    auto rv = [&](int e) { return r.e[e]; };
-    mul<false, true, false, true>(t, link(mu, pv), whole(link(nu, pu)));         // A1
-    mul<false, false, false, false>(r, link(nu, 0), t);                          // V A1
-    mul<false, false, false, false>(t, link(mu, mv), whole(link(nu, pu + mv)));  // A2
-    mul<true, false, true, false>(r, link(nu, mv), t);                           // + W^+ A2
-    mul<false, true, false, false>(q, rv, whole(link(mu, 0)));                   // ... U^+
-    mul<true, true, false, false>(t, link(mu, mm + pv), whole(link(nu, mm)));    // B1
-    mul<false, false, false, false>(r, link(nu, 0), t);                          // V B1
-    mul<true, false, false, true>(t, link(mu, mm + mv), whole(link(nu, mm + mv)));  // B2
-    mul<true, false, true, false>(r, link(nu, mv), t);                           // + W^+ B2
-    mul<false, false, true, false>(q, rv, whole(link(mu, mm)));                  // ... X
-    M3 f;
+  // (i csw / 16) (Q' - Q'^+): the diagonal, then (01 02 12) as (re, im)
+  auto herm = [&](const M3& q, double h[9]) {
+    const double w = 0.0625 * csw;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i) h[i] = -2.0 * w * q.e[4 * i].im;
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const C x = q.e[i * 3 + j], y = q.e[j * 3 + i];
-        const double re = 0.125 * (x.re - y.re), im = 0.125 * (x.im + y.im);
-        f.e[i * 3 + j] = C{-0.5 * csw * im, 0.5 * csw * re};
+    for (int k = 0; k < 3; ++k) {
+      const C x = q.e[k == 2 ? 5 : 1 + k], y = q.e[k == 0 ? 3 : k == 1 ? 6 : 7];
+      h[3 + 2 * k] = -w * (x.im + y.im);
+      h[4 + 2 * k] = w * (x.re - y.re);
+    }
+  };
+  // f = (i csw / 2) F of plane (mu, nu), Hermitian
+  auto plane = [&](int mu, int nu, int turn, double f[9]) {
+    const int k = (tid + 64 * turn) & (kThreads - 1);  // place in the list
+    const bool extra = k < count[mu];
+#pragma unroll 1
+    for (int pass = extra ? 0 : 1; pass < 2; ++pass) {
+      const int t = pass ? tid : list[mu][k];  // pass 0: T of the site before t
+      const long long down = dnL[mu][t], at = hereL[t] + (pass ? 0 : down);
+      const long long pu = pass ? pick(up, mu) : -down, pv = upL[nu - 1][t], mv = dnN[nu - 1][t];
+      M3 m, x, q;
+      auto rx = [&](int e) { return x.e[e]; };
+      mul<false, true, false, true>(m, link(at + pv, mu), whole(link(at + pu, nu)));
+      mul<false, false, false, false>(x, link(at, nu), m);
+      mul<false, false, false, false>(m, link(at + mv, mu), whole(link(at + pu + mv, nu)));
+      mul<true, false, true, false>(x, link(at + mv, nu), m);  // T
+      m = whole(link(at, mu));
+      mul<true, false, false, true>(q, rx, m);  // - T^+ U
+      double h[9];
+      herm(q, h);
+      double* to = pass ? &own[0][tid] : &far[0][t];
+#pragma unroll
+      for (int e = 0; e < 9; ++e) to[e * kThreads] = h[e];
+      if (pass) {
+        mul<false, true, false, false>(q, rx, m);  // T U^+
+        herm(q, f);
       }
-    return f;
+    }
+    __syncthreads();
+    const int from = mu == 0 ? before[0] : mu == 1 ? before[1] : before[2];
+    const double* h = from >= 0 ? &own[0][from] : &far[0][tid];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) f[e] += h[e * kThreads];
+    __syncthreads();
   };
   // entry (row, column) above the diagonal sits at pair 3 + its number in row-major order
   auto at = [&](int chi, int pair) { return ((long long)b * kCloverPairs + chi * 18 + pair) * g.bvol + l; };
@@ -149,8 +197,9 @@ __global__ void __launch_bounds__(kThreads, 2)
     for (int i = 0; i < 6; ++i) f0[i] = f5[i] = C{0.0, 0.0};
 #pragma unroll 1
     for (int q = 0; q < 2; ++q) {
-      const M3 f = plane(2 * q, 2 * q + 1);
-      const C v[6] = {f.e[0], f.e[4], f.e[8], f.e[1], f.e[2], f.e[5]};
+      double f[9];
+      plane(2 * q, 2 * q + 1, q, f);
+      const C v[6] = {{f[0], 0.0}, {f[1], 0.0}, {f[2], 0.0}, {f[3], f[4]}, {f[5], f[6]}, {f[7], f[8]}};
       const double is0 = q == 0 ? 1.0 : 0.0, is5 = 1.0 - is0;  // weights, not branches: a select of 24 registers spills
 #pragma unroll
       for (int i = 0; i < 6; ++i) {
@@ -168,15 +217,15 @@ __global__ void __launch_bounds__(kThreads, 2)
           d[sp][i] = C{sb.re[0][chi][3 * sp], sb.im[0][chi][3 * sp]} * f0[i];
           cmac(d[sp][i], C{sb.re[5][chi][3 * sp], sb.im[5][chi][3 * sp]}, f5[i]);
         }
-      out.put(at(chi, 0), C{d[0][0].re, d[0][1].re});
-      out.put(at(chi, 1), C{d[0][2].re, d[1][0].re});
-      out.put(at(chi, 2), C{d[1][1].re, d[1][2].re});
-      out.put(at(chi, 3), d[0][3]);
-      out.put(at(chi, 4), d[0][4]);
-      out.put(at(chi, 8), d[0][5]);
-      out.put(at(chi, 15), d[1][3]);
-      out.put(at(chi, 16), d[1][4]);
-      out.put(at(chi, 17), d[1][5]);
+      out.put(at(chi, 0), C{d[0][0].re, d[0][1].re}, active);
+      out.put(at(chi, 1), C{d[0][2].re, d[1][0].re}, active);
+      out.put(at(chi, 2), C{d[1][1].re, d[1][2].re}, active);
+      out.put(at(chi, 3), d[0][3], active);
+      out.put(at(chi, 4), d[0][4], active);
+      out.put(at(chi, 8), d[0][5], active);
+      out.put(at(chi, 15), d[1][3], active);
+      out.put(at(chi, 16), d[1][4], active);
+      out.put(at(chi, 17), d[1][5], active);
     }
   }
   C o[2][9];
@@ -184,12 +233,15 @@ __global__ void __launch_bounds__(kThreads, 2)
   for (int i = 0; i < 18; ++i) o[i / 9][i % 9] = C{0.0, 0.0};
 #pragma unroll 1
   for (int p = 1; p < 5; ++p) {  // xz, xt, yz, yt: planes 1..4 of the pairs mu < nu
-    const M3 f = plane(p > 2 ? 1 : 0, p % 2 ? 2 : 3);
+    double f[9];
+    plane(p > 2 ? 1 : 0, p % 2 ? 2 : 3, p + 1, f);
+    const C full[9] = {{f[0], 0.0}, {f[3], f[4]}, {f[5], f[6]}, {f[3], -f[4]}, {f[1], 0.0}, {f[7], f[8]},
+                       {f[5], -f[6]}, {f[7], -f[8]}, {f[2], 0.0}};
 #pragma unroll
     for (int chi = 0; chi < 2; ++chi) {
       const C sg = C{sb.re[p][chi][1], sb.im[p][chi][1]};
 #pragma unroll
-      for (int e = 0; e < 9; ++e) cmac(o[chi][e], sg, f.e[e]);
+      for (int e = 0; e < 9; ++e) cmac(o[chi][e], sg, full[e]);
     }
   }
 #pragma unroll
@@ -197,7 +249,7 @@ __global__ void __launch_bounds__(kThreads, 2)
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) out.put(at(chi, (a == 0 ? 5 : a == 1 ? 9 : 12) + c), o[chi][a * 3 + c]);
+      for (int c = 0; c < 3; ++c) out.put(at(chi, (a == 0 ? 5 : a == 1 ? 9 : 12) + c), o[chi][a * 3 + c], active);
 }
 
 }  // namespace
