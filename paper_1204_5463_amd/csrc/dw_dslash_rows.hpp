@@ -195,6 +195,10 @@ struct DCtl {
   const int* gate = nullptr;
   int gstride = 0;
   const double* dmass = nullptr;
+  // MODE 1: ||y||^2 of each block's sites to part[rhs * nblk + block]. The squares
+  // cost nothing beside the stores; a pass of its own reads y again (32^3x64: 80 us
+  // after the 564 us of b - D x)
+  s64* part = nullptr;
 };
 
 // threads of a workgroup: a block's sites in groups of 32, two lanes each
@@ -296,6 +300,7 @@ __global__ void __launch_bounds__(MAXT)
       cd[a] = r ? w[3 + a] : got;
     }
   }
+  double sq = 0;
   if (active) {
     const T half = (T)0.5;
 #pragma unroll
@@ -307,11 +312,27 @@ __global__ void __launch_bounds__(MAXT)
         cplx<T> acc = q ? lowzt[a] : up[a];
         if constexpr (CLOV) acc -= (T)2 * (q ? cd[a] : cu[a]);
         cplx<T> d = scale * (diag * psi - half * acc);
-        if constexpr (MODE == 1) d = ld<T>(bsrc + (long long)rhs * ys + own(k)) - d;
+        if constexpr (MODE == 1) {
+          d = ld<T>(bsrc + (long long)rhs * ys + own(k)) - d;
+          sq = fma((double)d.re, (double)d.re, fma((double)d.im, (double)d.im, sq));
+        }
         if constexpr (CANON) st(yr + own(k), d);
         else st_nt(yr + own(k), d);
       }
   }
+  if constexpr (MODE == 1)
+    if (dc.part) {
+      sq = wave_total(sq);
+      __syncthreads();  // the spinor in LDS is read out
+      double* red = reinterpret_cast<double*>(smem);
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        double t = red[0];
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t += red[w];
+        dc.part[(long long)rhs * g.nblk + b] = s64{t, 0.0};
+      }
+    }
 }
 
 }  // namespace dw

@@ -225,7 +225,9 @@ dw_status launch_dslash_outer(const Geom& g, double m0, int prec_x, const void* 
                               double* y, const double* b, int mode, int nrhs, long long x_rhs_stride,
                               long long y_rhs_stride, hipStream_t s, const int* rlist = nullptr,
                               const void* C64 = nullptr, const int* gate = nullptr, int gstride = 0,
-                              const double* dmass = nullptr);
+                              const double* dmass = nullptr, void* part = nullptr);
+// part (device, may be null): ||y||^2 by blocks, nblk pairs (sum, 0) per right-hand
+// side; mode 1, FP64 x and blocks that dslash_canonical_fits takes
 // y = D x on canonical FP64 fields, no packing pass; for blocks that
 // dslash_canonical_fits takes
 bool dslash_canonical_fits(const Geom& g);

@@ -19,6 +19,10 @@ constexpr int kLd = kMaxM + 1;   // leading dimension of small matrices
 dw_status blas_dots(int prec_v, const void* V, long long stride, int ncols, const double* w, long long n,
                     double* partials, double* out, int ostride, int op, hipStream_t s, const int* gate = nullptr,
                     const int* dn = nullptr, int dadd = 0);
+// rr[0] <- the sum of G pairs (real part); scale[0] <- sqrt(n / rr) (1 for rr = 0 or
+// unit), scale[1], scale[2] <- 1 / scale[0], 0 (all device doubles)
+dw_status blas_rms_scale(const void* partials, int G, long long n, bool unit, double* rr, double* scale,
+                         hipStream_t s);
 // y = alpha[0] * x (alpha a device double)
 dw_status blas_scale(const double* x, double* y, const double* alpha, long long n, hipStream_t s,
                      const int* gate = nullptr);

@@ -371,10 +371,15 @@ dw_status launch_c(const Geom& g, T diag, const SX* x, T scale, const SG* U, SY*
 dw_status launch_dslash_outer(const Geom& g, double m0, int prec_x, const void* x, double scale, const void* U64,
                               double* y, const double* b, int mode, int nrhs, long long xs, long long ys,
                               hipStream_t s, const int* rlist, const void* C64, const int* gate, int gstride,
-                              const double* dmass) {
+                              const double* dmass, void* part) {
   if (nrhs < 1) return DW_OK;
+  if (part && (mode != 1 || prec_x != DW_PREC_F64 || !dslash_canonical_fits(g))) {
+    set_error("outer dslash: no norm from this form");
+    return DW_EINVAL;
+  }
   const double diag = 4.0 + m0;
   DCtl dc;
+  dc.part = (s64*)part;
   dc.gate = gate;
   dc.gstride = gstride;
   dc.dmass = dmass;

@@ -474,52 +474,65 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   const long long n = g.V * 12;
   const int prec = sp->storage;
   const int zprec = prec == DW_PREC_F64 ? DW_PREC_F64 : DW_PREC_F32;
-  DevBuf bi, xi, ri, vi, zi, part, nrm, one;
+  DevBuf bi, xi, ri, vi, zi, part, hist, scale;
   DW_TRY(bi.alloc(f->ctx, (size_t)n * 16, stream));
   DW_TRY(xi.alloc(f->ctx, (size_t)n * 16, stream));
   DW_TRY(ri.alloc(f->ctx, (size_t)n * 16, stream));
   DW_TRY(vi.alloc(f->ctx, (size_t)n * pair_bytes(prec), stream));
   DW_TRY(zi.alloc(f->ctx, (size_t)n * pair_bytes(zprec), stream));
-  DW_TRY(part.alloc(f->ctx, (size_t)kBlasGrid * 16, stream));
-  DW_TRY(nrm.alloc(f->ctx, 16, stream));
-  DW_TRY(one.alloc(f->ctx, 16, stream));
-  static const double kOne[2] = {1.0, 0.0};
-  DW_CHECK_HIP(hipMemcpyAsync(one.p, kOne, sizeof kOne, hipMemcpyHostToDevice, stream));
-  DW_TRY(launch_pack_spinor(g, DW_PREC_F64, b, bi.p, 1.0, 1, stream));
-  DW_CHECK_HIP(hipMemsetAsync(xi.p, 0, (size_t)n * 16, stream));
-  auto sqnorm = [&](const void* v, double& out) -> dw_status {
-    DW_TRY(blas_dots(DW_PREC_F64, v, n, 1, (const double*)v, n, part.as<double>(), nrm.as<double>(), 1, 0, stream));
-    double h[2];
-    DW_CHECK_HIP(hipMemcpyAsync(h, nrm.p, sizeof h, hipMemcpyDeviceToHost, stream));
+  // the norms come from the operator's launch where its form gives them
+  const bool fused = dslash_canonical_fits(g);
+  DW_TRY(part.alloc(f->ctx, (size_t)(kBlasGrid > g.nblk ? kBlasGrid : g.nblk) * 16, stream));
+  constexpr int kHist = 512;  // iterations between two looks at the norms
+  DW_TRY(hist.alloc(f->ctx, kHist * 16, stream));
+  DW_TRY(scale.alloc(f->ctx, 32, stream));
+  double h[2 * kHist];
+  auto fetch = [&](int count) -> dw_status {
+    DW_CHECK_HIP(hipMemcpyAsync(h, hist.p, (size_t)count * 16, hipMemcpyDeviceToHost, stream));
     DW_CHECK_HIP(hipStreamSynchronize(stream));
-    out = h[0];
     return DW_OK;
   };
-  double bb;
-  DW_TRY(sqnorm(bi.p, bb));
+  auto sqnorm = [&](const void* v, int slot) {
+    return blas_dots(DW_PREC_F64, v, n, 1, (const double*)v, n, part.as<double>(), hist.as<double>() + 2 * slot, 1, 0,
+                     stream);
+  };
+  DW_TRY(launch_pack_spinor(g, DW_PREC_F64, b, bi.p, 1.0, 1, stream));
+  DW_CHECK_HIP(hipMemsetAsync(xi.p, 0, (size_t)n * 16, stream));
+  DW_TRY(sqnorm(bi.p, 0));
+  DW_TRY(fetch(1));
+  const double bb = h[0];
   if (!(bb > 0)) {
     set_error("sap_solve: b = 0");
     return DW_EINVAL;
   }
   const double bnorm = sqrt(bb);
+  const bool unit = prec == DW_PREC_F64;
+  double* sc = scale.as<double>();
   for (int k = 0; k <= niter; ++k) {
+    const int slot = k % kHist;
+    double* rr = hist.as<double>() + 2 * slot;
     // r = b - D x_k (FP64 links, clover and arithmetic)
     DW_TRY(launch_dslash_outer(g, m0, DW_PREC_F64, xi.p, 1.0, f->U[DW_PREC_F64], ri.as<double>(), bi.as<double>(), 1,
-                               1, n, n, stream, nullptr, f->C[DW_PREC_F64]));
-    double rr;
-    DW_TRY(sqnorm(ri.p, rr));
-    resid[k] = sqrt(rr) / bnorm;
-    if (rr == 0) {
-      for (int j = k + 1; j <= niter; ++j) resid[j] = 0;
-      break;
+                               1, n, n, stream, nullptr, f->C[DW_PREC_F64], nullptr, 0, nullptr,
+                               fused ? part.p : nullptr));
+    if (!fused) DW_TRY(sqnorm(ri.p, slot));
+    DW_TRY(fused ? blas_rms_scale(part.p, g.nblk, n, unit, rr, sc, stream)
+                 : blas_rms_scale(rr, 1, n, unit, rr, sc, stream));
+    if (slot == kHist - 1 || k == niter) {
+      DW_TRY(fetch(slot + 1));
+      for (int j = 0; j <= slot; ++j) resid[k - slot + j] = sqrt(h[2 * j]) / bnorm;
+      if (h[2 * slot] == 0) {
+        for (int j = k + 1; j <= niter; ++j) resid[j] = 0;
+        break;
+      }
     }
     if (k == niter || sp->ncycles == 0) continue;  // M = 0 without cycles
     // x_{k+1} = x_k + M r: the preconditioner input at storage precision,
-    // scaled to unit RMS (M is scale-equivariant), the correction added in FP64
-    const double sigma = prec == DW_PREC_F64 ? 1.0 : sqrt((double)n / rr);
-    DW_TRY(launch_convert(DW_PREC_F64, ri.p, prec, vi.p, sigma, n, stream));
+    // scaled to unit RMS (M is scale-equivariant), the correction added in FP64.
+    // From r = 0 on M r = 0 and x stays
+    DW_TRY(launch_convert(DW_PREC_F64, ri.p, prec, vi.p, 1.0, n, stream, sc));
     DW_TRY(sap_apply_internal(f, m0, sp, vi.p, zi.p, 1, stream));
-    DW_TRY(blas_combine(zprec, zi.p, n, 1, one.as<double>(), 1.0 / sigma, xi.as<double>(), n, stream));
+    DW_TRY(blas_combine(zprec, zi.p, n, 1, sc + 1, 1.0, xi.as<double>(), n, stream));
   }
   DW_TRY(launch_unpack_spinor(g, DW_PREC_F64, xi.p, x, 1.0, 1, stream));
   DW_CHECK_HIP(hipStreamSynchronize(stream));
