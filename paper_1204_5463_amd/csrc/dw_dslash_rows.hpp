@@ -17,7 +17,7 @@
 // CANON: x, y and b in the canonical layout (12 contiguous complex numbers per
 // site), so that an application on caller fields needs no packing pass: packing,
 // the operator on the internal layout and unpacking moved 2.7 times the bytes
-// (32^3x64, 12 right-hand sides: 8931 -> 5260 us per application; 8^4: 22.5 ->
+// (32^3x64, 12 right-hand sides: 8931 -> 5180 us per application; 8^4: 22.5 ->
 // 12.0 us, one launch for three and no allocation).
 //
 // Bound: memory. At 12 right-hand sides the launch moves about 0.8 KB per site
@@ -161,6 +161,7 @@ __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx
     }
   }
   if constexpr (!SHIFT) __syncthreads();
+  if constexpr (BS == 4) __builtin_amdgcn_sched_barrier(0);
   if (c.active) {
     if (c.lc[MU] > 0) {
 #pragma unroll
@@ -186,6 +187,7 @@ __device__ __forceinline__ void dir(const Ctx<T, SX, SG>& c, cplx<T> up[3], cplx
     }
   }
   if constexpr (MU < 3 && !SHIFT) __syncthreads();
+  if constexpr (BS == 4) __builtin_amdgcn_sched_barrier(0);
 }
 
 }  // namespace rows
@@ -211,23 +213,17 @@ size_t rows_lds(const Geom& g) {
 template <typename T, typename SX>
 bool rows_fits(const Geom& g) { return rows_threads(g) <= 1024 && rows_lds<T, SX>(g) <= 160 * 1024; }
 
-// 4^4 blocks, at most one workgroup per CU: a launch is one chain of loads and
-// barriers, which the BS = 4 form shortens (8^4, dw_apply: 13.5 -> 12.0 us, 192
-// workgroups 17.2 -> 15.7, 256: 21.1 -> 19.1). From the second workgroup per CU on
-// its registers cost more than the latency gives (384: 26.1 -> 28.9 us, 512: 34.0 ->
-// 34.4, 6144: 320 -> 383). The two forms do the same arithmetic, bit for bit.
-inline bool rows_alone(const Geom& g, int nrhs) {
-  constexpr int kCUs = 256;
-  return g.nblk * nrhs <= kCUs && g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4;
-}
-
 // MODE 0: y = scale * D x; MODE 1: y = b - scale * D x
 // MAXT: largest workgroup of the instantiation, 1024 for blocks above 256 sites.
 // Promising 512 where that holds lets the compiler order the loads for the four
 // waves a SIMD has registers for (32^3 x 64, 12 sides: 5525 -> 5260 us).
-// BS: 4 for 4^4 blocks known at compile time, else 0. With the strides constant
-// the compiler has all loads of a site in flight at once, at 148 to 188 registers:
-// two waves per SIMD. rows_alone() says where that is the better trade.
+// BS: 4 for 4^4 blocks known at compile time, else 0. Strides and limits are
+// constants, and the x and y products go to the neighbour by lane shifts (four of
+// the eight barriers and half of the handing over through LDS less): 8^4, dw_apply:
+// 13.5 -> 12.0 us, 16^3x32 33.9 -> 32.8, 12 sides 319.5 -> 314.4, 32^3x64 with 12 5270
+// -> 5182. The scheduling fences keep each direction's loads with it: without them
+// all loads of a site are hoisted, 188 registers and two waves per SIMD (32^3x64
+// with 12 sides 6370 us).
 template <typename T, typename SX, typename SG, typename SY, int MODE, int MAXT, int BS, bool CLOV, bool CANON>
 __global__ void __launch_bounds__(MAXT)
     k_dslash_rows(Geom g, T diag, const SX* __restrict__ x, T scale, const SG* __restrict__ U, SY* __restrict__ y,

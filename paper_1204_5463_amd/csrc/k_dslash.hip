@@ -31,6 +31,8 @@ constexpr int kThreads = 256;
 // + 24 accumulation) - 24 (first accumulation is a copy) + 48 (diagonal)
 constexpr double kFlopsPerSite = 1368.0;
 
+bool cube4(const Geom& g) { return g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4; }
+
 // ---- block-staged kernel ---------------------------------------------------------
 template <typename T, typename SX, typename SG>
 struct BlkCtx {
@@ -45,11 +47,27 @@ struct BlkCtx {
   const SG* U;
 };
 
-template <int MU, typename T, typename SX, typename SG>
+// BS = 4 (4^4 blocks known at compile time): a wavefront holds one t slice with x
+// fastest, so what x, y and z hops hand over stays within it and only the t
+// products cross wavefronts. Two barriers per launch instead of nine.
+template <bool WAVE>
+__device__ __forceinline__ void blk_sync() {
+  if constexpr (WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // the next direction's loads stay behind: hoisted, they cost registers
+    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    __syncthreads();
+  }
+}
+
+template <int MU, int BS, typename T, typename SX, typename SG>
 __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[12], const cplx<T> psi[12]) {
   const Geom& g = c.g;
-  const int bvol = g.bvol, l = c.l;
-  const int st = g.lstride[MU];
+  const int bvol = BS ? BS * BS * BS * BS : g.bvol, l = c.l, bm = BS ? BS : g.B[MU];
+  const int st = BS ? (MU == 0 ? 1 : MU == 1 ? BS : MU == 2 ? BS * BS : BS * BS * BS) : g.lstride[MU];
   cplx<T> h0[3], h1[3], g0[3], g1[3];
   if (c.active) {
     cplx<T> w[9];
@@ -65,18 +83,18 @@ __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[
       c.pb[(3 + a) * bvol + l] = g1[a];
     }
     // forward hop: (1 - g_mu) U_mu(n) psi(n + mu)
-    if (c.lc[MU] < g.B[MU] - 1) {
+    if (c.lc[MU] < bm - 1) {
       proj<MU, +1, T>([&](int k) { return ld<T>(c.xsh + k * bvol + l + st); }, h0, h1);
     } else {
       int c2[4] = {c.bc[0], c.bc[1], c.bc[2], c.bc[3]};
       c2[MU] = (c.bc[MU] + 1 == g.N[MU]) ? 0 : c.bc[MU] + 1;
-      const int nb = encode_block(g, c2), nl = l - (g.B[MU] - 1) * st;
+      const int nb = encode_block(g, c2), nl = l - (bm - 1) * st;
       proj<MU, +1, T>([&](int k) { return ld<T>(c.xr + spinor_index(g, nb, k, nl)); }, h0, h1);
     }
     su3_mul<false, T>(wl, h0, h1, g0, g1);
     recon_acc<MU, +1, T>(acc, g0, g1);
   }
-  __syncthreads();
+  blk_sync<BS == 4 && MU < 3>();
   if (c.active) {
     if (c.lc[MU] > 0) {
 #pragma unroll
@@ -87,13 +105,13 @@ __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[
     } else {
       int c2[4] = {c.bc[0], c.bc[1], c.bc[2], c.bc[3]};
       c2[MU] = (c.bc[MU] == 0) ? g.N[MU] - 1 : c.bc[MU] - 1;
-      const int nb = encode_block(g, c2), nl = l + (g.B[MU] - 1) * st;
+      const int nb = encode_block(g, c2), nl = l + (bm - 1) * st;
       proj<MU, -1, T>([&](int k) { return ld<T>(c.xr + spinor_index(g, nb, k, nl)); }, h0, h1);
       su3_mul<true, T>([&](int e) { return ld<T>(c.U + gauge_index(g, nb, MU, e, nl)); }, h0, h1, g0, g1);
     }
     recon_acc<MU, -1, T>(acc, g0, g1);
   }
-  __syncthreads();
+  if constexpr (BS != 4) __syncthreads();
 }
 
 // FP16 spinors and links: the same scheme with packed FP16 operands. The
@@ -102,11 +120,11 @@ __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[
 // products accumulated in FP32 (exact products), so a hop is 36 dot
 // products, 12 packed adds and the FP32 rebuild. psi16 holds the site's
 // own spinor as packed (re, im) pairs.
-template <int MU, typename SX, typename SG>
+template <int MU, int BS, typename SX, typename SG>
 __device__ __forceinline__ void blk_dir16(const BlkCtx<float, SX, SG>& c, cplx<float> acc[12], const h2v psi16[12]) {
   const Geom& g = c.g;
-  const int bvol = g.bvol, l = c.l;
-  const int st = g.lstride[MU];
+  const int bvol = BS ? BS * BS * BS * BS : g.bvol, l = c.l, bm = BS ? BS : g.B[MU];
+  const int st = BS ? (MU == 0 ? 1 : MU == 1 ? BS : MU == 2 ? BS * BS : BS * BS * BS) : g.lstride[MU];
   const h2v* xsh = reinterpret_cast<const h2v*>(c.xsh);
   const h2v* xr = reinterpret_cast<const h2v*>(c.xr);
   const h2v* U = reinterpret_cast<const h2v*>(c.U);
@@ -124,16 +142,16 @@ __device__ __forceinline__ void blk_dir16(const BlkCtx<float, SX, SG>& c, cplx<f
       c.pb[(3 + a) * bvol + l] = g1[a];
     }
     // forward hop: (1 - g_mu) U_mu(n) psi(n + mu)
-    if (c.lc[MU] < g.B[MU] - 1) {
+    if (c.lc[MU] < bm - 1) {
       hop16p<MU, +1>(acc, [&](int k) { return xsh[k * bvol + l + st]; }, wl);
     } else {
       int c2[4] = {c.bc[0], c.bc[1], c.bc[2], c.bc[3]};
       c2[MU] = (c.bc[MU] + 1 == g.N[MU]) ? 0 : c.bc[MU] + 1;
-      const int nb = encode_block(g, c2), nl = l - (g.B[MU] - 1) * st;
+      const int nb = encode_block(g, c2), nl = l - (bm - 1) * st;
       hop16p<MU, +1>(acc, [&](int k) { return xr[spinor_index(g, nb, k, nl)]; }, wl);
     }
   }
-  __syncthreads();
+  blk_sync<BS == 4 && MU < 3>();
   if (c.active) {
     if (c.lc[MU] > 0) {
 #pragma unroll
@@ -145,18 +163,18 @@ __device__ __forceinline__ void blk_dir16(const BlkCtx<float, SX, SG>& c, cplx<f
     } else {
       int c2[4] = {c.bc[0], c.bc[1], c.bc[2], c.bc[3]};
       c2[MU] = (c.bc[MU] == 0) ? g.N[MU] - 1 : c.bc[MU] - 1;
-      const int nb = encode_block(g, c2), nl = l + (g.B[MU] - 1) * st;
+      const int nb = encode_block(g, c2), nl = l + (bm - 1) * st;
       hop16p<MU, -1>(acc, [&](int k) { return xr[spinor_index(g, nb, k, nl)]; },
                      [&](int e) { return U[gauge_index(g, nb, MU, e, nl)]; });
     }
   }
-  __syncthreads();
+  if constexpr (BS != 4) __syncthreads();
 }
 
 __host__ __device__ constexpr size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
 // CLOV: add the clover term (site-local, dw_clover.hpp) from Cl.
-template <typename T, typename SX, typename SG, typename SY, int MODE, int MAXT, bool CLOV>
+template <typename T, typename SX, typename SG, typename SY, int MODE, int MAXT, int BS, bool CLOV>
 __global__ void __launch_bounds__(MAXT)
     k_dslash_blk(Geom g, T diag, const SX* __restrict__ x, T scale, const SG* __restrict__ U, SY* __restrict__ y,
                  const SY* __restrict__ bsrc, long long xs, long long ys, int nr, const int* __restrict__ rlist,
@@ -202,15 +220,15 @@ __global__ void __launch_bounds__(MAXT)
   __syncthreads();
   const BlkCtx<T, SX, SG> c{g, b, l, active, bc, lc, xr, xsh, pb, U};
   if constexpr (P16) {
-    blk_dir16<0>(c, acc, psi16);
-    blk_dir16<1>(c, acc, psi16);
-    blk_dir16<2>(c, acc, psi16);
-    blk_dir16<3>(c, acc, psi16);
+    blk_dir16<0, BS>(c, acc, psi16);
+    blk_dir16<1, BS>(c, acc, psi16);
+    blk_dir16<2, BS>(c, acc, psi16);
+    blk_dir16<3, BS>(c, acc, psi16);
   } else {
-    blk_dir<0>(c, acc, psi);
-    blk_dir<1>(c, acc, psi);
-    blk_dir<2>(c, acc, psi);
-    blk_dir<3>(c, acc, psi);
+    blk_dir<0, BS>(c, acc, psi);
+    blk_dir<1, BS>(c, acc, psi);
+    blk_dir<2, BS>(c, acc, psi);
+    blk_dir<3, BS>(c, acc, psi);
   }
   if (active) {
     const T half = (T)0.5;
@@ -236,6 +254,18 @@ __global__ void __launch_bounds__(MAXT)
 template <typename T, typename SX>
 size_t blk_lds(const Geom& g) {
   return align16((size_t)12 * g.bvol * sizeof(SX)) + (size_t)6 * g.bvol * sizeof(cplx<T>);
+}
+
+// Where the BS = 4 form runs (us, general -> BS = 4): 16-bit storage on all grids (FP16
+// 16^3x32 12.3 -> 11.6, 24^3x48 with 4 right-hand sides 133.6 -> 127.4, with the
+// clover term 62.1 -> 54.7, 32^3x64 130.7 -> 127.4; BF16 154.2 -> 132.9 and 150.0 ->
+// 138.8), FP32 up to 4096 workgroups (16 workgroups 12.5 -> 10.0, 512 19.0 -> 17.1, 2048
+// 50.3 -> 46.4). Beyond, FP32 is bound by traffic and the barriers keep the wavefronts
+// of a block together on its lines (8192 266.1 -> 267.8, 10368 277.4 -> 280.4). The
+// two forms do the same arithmetic, bit for bit.
+template <typename SX>
+bool blk_by_wave(const Geom& g, int nrhs) {
+  return cube4(g) && (sizeof(SX) == 4 || (long long)g.nblk * nrhs <= 4096);
 }
 
 // ---- gather kernel (blocks too large for LDS staging) -------------------------------
@@ -321,7 +351,7 @@ dw_status launch_rows(const Geom& g, T diag, const SX* x, T scale, const SG* U, 
     DW_CHECK_LAUNCH();
     return DW_OK;
   };
-  if (rows_alone(g, nrhs)) return go(k_dslash_rows<T, SX, SG, SY, MODE, 512, 4, CLOV, CANON>);
+  if (cube4(g)) return go(k_dslash_rows<T, SX, SG, SY, MODE, 512, 4, CLOV, CANON>);
   if (threads <= 512) return go(k_dslash_rows<T, SX, SG, SY, MODE, 512, 0, CLOV, CANON>);
   return go(k_dslash_rows<T, SX, SG, SY, MODE, 1024, 0, CLOV, CANON>);
 }
@@ -348,9 +378,12 @@ dw_status launch_any(const Geom& g, T diag, const SX* x, T scale, const SG* U, S
       DW_CHECK_LAUNCH();
       return DW_OK;
     };
-    if (threads <= 256) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 256, CLOV>);
-    if (threads <= 512) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 512, CLOV>);
-    return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 1024, CLOV>);
+    if constexpr (!kRows<T>) {  // the two-lane form has taken blocks up to 512 sites
+      if (blk_by_wave<SX>(g, nrhs)) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 256, 4, CLOV>);
+      if (threads <= 256) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 256, 0, CLOV>);
+      if (threads <= 512) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 512, 0, CLOV>);
+    }
+    return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 1024, 0, CLOV>);
   }
   hipLaunchKernelGGL((k_dslash<T, SX, SG, SY, MODE, CLOV>), grid_for(g, nrhs), kThreads, 0, s, g, diag, x, scale, U,
                      y, b, xs, ys, nrhs, rlist, Cl, dc);

@@ -52,9 +52,9 @@ def test_fp64_operator_block_edges(dwctx, block, csw):
 
 @pytest.mark.parametrize("csw", [0.0, 1.9])
 def test_fp64_operator_4x4x4x4_forms(dwctx, csw):
-    """4^4 blocks: 16 blocks x 16 right-hand sides is the largest launch of the
-    one-workgroup-per-CU form, 17 the smallest of the general one. The oracle
-    bound at the first and last right-hand side, and the same bits from both."""
+    """4^4 blocks have a form of their own; 16 blocks x 16 right-hand sides fill
+    the CUs once, 17 do not. The oracle bound at the first and last right-hand
+    side, and the same bits from both launches."""
     L, block, m0 = (8, 8, 8, 8), (4, 4, 4, 4), -0.4
     U = synth.gauge_field(L, 0.7, 5)
     f = P.Field(dwctx, L, block, P.to_device(U))
@@ -79,4 +79,26 @@ def test_fp64_operator_4x4x4x4_forms(dwctx, csw):
             assert np.max(np.abs(y[r].numpy() - ref)) <= 2e-14 * np.max(np.abs(ref)), r
     for a, b in zip(out[16], out[17]):
         assert torch.equal(a, b[:16])
+    f.close()
+
+
+@pytest.mark.parametrize("csw", [0.0, 1.9])
+def test_fp32_operator_4x4x4x4_forms(dwctx, csw):
+    """FP32 storage: 16 blocks x 256 right-hand sides is the largest launch of the
+    form for small grids, 257 the smallest of the general one: the same bits, and
+    the FP64 operator to 4 x 2^-24 of the norm (roundings of inputs and hops)."""
+    L, block, m0 = (8, 8, 8, 8), (4, 4, 4, 4), -0.4
+    f = P.Field(dwctx, L, block, P.to_device(synth.gauge_field(L, 0.7, 5)))
+    if csw:
+        f.set_clover(csw)
+    x = P.to_device(synth.gaussian_spinors(L, 3)).repeat((86,) + (1,) * 6)[:257].contiguous()
+    xi = f.pack(P.DW_PREC_F32, x)
+    out = []
+    for nr in (256, 257):
+        yi = torch.zeros_like(xi)
+        f.apply_ex(m0, P.DW_PREC_F32, xi, yi, nrhs=nr)
+        out.append(f.unpack(P.DW_PREC_F32, yi, nrhs=nr)[:256])
+    assert torch.equal(out[0], out[1])
+    ref = f.apply(m0, x[:3].contiguous())
+    assert torch.linalg.vector_norm(out[0][:3] - ref) <= 4 * 2.0 ** -24 * torch.linalg.vector_norm(ref)
     f.close()
