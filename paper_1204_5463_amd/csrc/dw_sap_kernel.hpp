@@ -1,6 +1,8 @@
 // One colour of the Schwarz alternating procedure (paper Section 2, Alg. 2):
 // the kernel template and its launch-shape selection, instantiated once per
 // storage precision by k_sap_<prec>.hip.
+// FP64 and FP32 storage on 4^4 blocks take the two-threads-per-site form of
+// dw_sap_split.hpp instead.
 //
 // One workgroup per block of the given colour; blocks of one colour do not
 // couple (red/black colouring with an even block count per direction), so
