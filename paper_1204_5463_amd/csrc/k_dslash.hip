@@ -49,7 +49,9 @@ struct BlkCtx {
 
 // BS = 4 (4^4 blocks known at compile time): a wavefront holds one t slice with x
 // fastest, so what x, y and z hops hand over stays within it and only the t
-// products cross wavefronts. Two barriers per launch instead of nine.
+// products cross wavefronts. Two barriers per launch instead of nine; within the
+// wavefront the LDS serves its accesses in order, and blk_sync keeps the compiler
+// from moving a load of one lane's product past the store that replaces it.
 template <bool WAVE>
 __device__ __forceinline__ void blk_sync() {
   if constexpr (WAVE) {
@@ -111,7 +113,8 @@ __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[
     }
     recon_acc<MU, -1, T>(acc, g0, g1);
   }
-  if constexpr (BS != 4) __syncthreads();
+  // the products taken are read before the next direction's replace them
+  if constexpr (BS != 4 || MU < 3) blk_sync<BS == 4>();
 }
 
 // FP16 spinors and links: the same scheme with packed FP16 operands. The
@@ -168,7 +171,8 @@ __device__ __forceinline__ void blk_dir16(const BlkCtx<float, SX, SG>& c, cplx<f
                      [&](int e) { return U[gauge_index(g, nb, MU, e, nl)]; });
     }
   }
-  if constexpr (BS != 4) __syncthreads();
+  // the products taken are read before the next direction's replace them
+  if constexpr (BS != 4 || MU < 3) blk_sync<BS == 4>();
 }
 
 __host__ __device__ constexpr size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
