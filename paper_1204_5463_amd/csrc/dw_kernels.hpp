@@ -4,6 +4,8 @@
 // dimension kLd (row i, column j at i + j*kLd).
 #pragma once
 
+#include <stddef.h>
+
 #include "dw_internal.hpp"
 
 namespace dw {
@@ -19,9 +21,15 @@ constexpr int kLd = kMaxM + 1;   // leading dimension of small matrices
 dw_status blas_dots(int prec_v, const void* V, long long stride, int ncols, const double* w, long long n,
                     double* partials, double* out, int ostride, int op, hipStream_t s, const int* gate = nullptr,
                     const int* dn = nullptr, int dadd = 0);
-// rr[0] <- the sum of G pairs (real part); scale[0] <- sqrt(n / rr) (1 for rr = 0 or
-// unit), scale[1], scale[2] <- 1 / scale[0], 0 (all device doubles)
-dw_status blas_rms_scale(const void* partials, int G, long long n, bool unit, double* rr, double* scale,
+// A scale on the device and its inverse as a complex coefficient, which
+// blas_combine loads as one 16-byte pair.
+struct alignas(16) RmsScale {
+  double scale, unused;
+  double inverse[2];  // (1 / scale, 0)
+};
+static_assert(offsetof(RmsScale, inverse) % 16 == 0, "a pair is loaded at once");
+// rr[0] <- the sum of G pairs (real part); the scale <- sqrt(n / rr) (1 for rr = 0 or unit)
+dw_status blas_rms_scale(const void* partials, int G, long long n, bool unit, double* rr, RmsScale* scale,
                          hipStream_t s);
 // y = alpha[0] * x (alpha a device double)
 dw_status blas_scale(const double* x, double* y, const double* alpha, long long n, hipStream_t s,

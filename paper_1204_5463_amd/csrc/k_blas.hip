@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(kThreads)
 // device: fetching the norm first left the GPU idle for about 50 us per iteration.
 __global__ void __launch_bounds__(kThreads)
     k_rms_scale(const s64* __restrict__ partials, int G, double n, bool unit, double* __restrict__ rr,
-                double* __restrict__ scale) {
+                RmsScale* __restrict__ scale) {
   __shared__ double red[kThreads / kWave];
   double a = 0;
   for (int g = threadIdx.x; g < G; g += kThreads) a += partials[g].x;
@@ -149,9 +149,7 @@ __global__ void __launch_bounds__(kThreads)
     for (int q = 0; q < kThreads / kWave; ++q) a += red[q];
     const double sc = unit || a == 0 ? 1.0 : sqrt(n / a);
     rr[0] = a;
-    scale[0] = sc;
-    scale[1] = 1.0 / sc;
-    scale[2] = 0.0;
+    *scale = RmsScale{sc, 0.0, {1.0 / sc, 0.0}};
   }
 }
 
@@ -449,7 +447,7 @@ dw_status blas_dots(int prec_v, const void* V, long long stride, int ncols, cons
   return DW_OK;
 }
 
-dw_status blas_rms_scale(const void* partials, int G, long long n, bool unit, double* rr, double* scale,
+dw_status blas_rms_scale(const void* partials, int G, long long n, bool unit, double* rr, RmsScale* scale,
                          hipStream_t s) {
   KTimer kt(DW_K_REDUCE, s);
   hipLaunchKernelGGL(k_rms_scale, 1, kThreads, 0, s, (const s64*)partials, G, (double)n, unit, rr, scale);

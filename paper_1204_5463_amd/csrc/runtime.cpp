@@ -485,7 +485,7 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   DW_TRY(part.alloc(f->ctx, (size_t)(kBlasGrid > g.nblk ? kBlasGrid : g.nblk) * 16, stream));
   constexpr int kHist = 512;  // iterations between two looks at the norms
   DW_TRY(hist.alloc(f->ctx, kHist * 16, stream));
-  DW_TRY(scale.alloc(f->ctx, 32, stream));
+  DW_TRY(scale.alloc(f->ctx, sizeof(RmsScale), stream));
   double h[2 * kHist];
   auto fetch = [&](int count) -> dw_status {
     DW_CHECK_HIP(hipMemcpyAsync(h, hist.p, (size_t)count * 16, hipMemcpyDeviceToHost, stream));
@@ -507,7 +507,7 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   }
   const double bnorm = sqrt(bb);
   const bool unit = prec == DW_PREC_F64;
-  double* sc = scale.as<double>();
+  RmsScale* const sc = scale.as<RmsScale>();
   for (int k = 0; k <= niter; ++k) {
     const int slot = k % kHist;
     double* rr = hist.as<double>() + 2 * slot;
@@ -530,9 +530,9 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
     // x_{k+1} = x_k + M r: the preconditioner input at storage precision,
     // scaled to unit RMS (M is scale-equivariant), the correction added in FP64.
     // From r = 0 on M r = 0 and x stays
-    DW_TRY(launch_convert(DW_PREC_F64, ri.p, prec, vi.p, 1.0, n, stream, sc));
+    DW_TRY(launch_convert(DW_PREC_F64, ri.p, prec, vi.p, 1.0, n, stream, &sc->scale));
     DW_TRY(sap_apply_internal(f, m0, sp, vi.p, zi.p, 1, stream));
-    DW_TRY(blas_combine(zprec, zi.p, n, 1, sc + 1, 1.0, xi.as<double>(), n, stream));
+    DW_TRY(blas_combine(zprec, zi.p, n, 1, sc->inverse, 1.0, xi.as<double>(), n, stream));
   }
   DW_TRY(launch_unpack_spinor(g, DW_PREC_F64, xi.p, x, 1.0, 1, stream));
   DW_CHECK_HIP(hipStreamSynchronize(stream));
