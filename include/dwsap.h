@@ -206,19 +206,21 @@ int64_t dw_field_volume(dw_field field);
 /* y = D x for nrhs right-hand sides, FP64 (eq. 1). x and y: canonical
  * spinor arrays of nrhs * V * 12 complex128 each; they must not overlap.
  * Asynchronous on `stream`. Blocks of up to 512 sites need no temporaries;
- * above, internal-layout copies of x and y come from the context's allocator
- * and go back to it in stream order. */
+ * above, and for x and y that do overlap, internal-layout copies of x and y come
+ * from the context's allocator and go back to it in stream order. x == y is
+ * refused (DW_EINVAL). */
 dw_status dw_apply(dw_field field, double m0, const double* x, double* y, int32_t nrhs, hipStream_t stream);
 
 /* y = D x as dw_apply, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc). It calls no allocator: for blocks above 512 sites the
- * internal-layout copies of x and y use a fixed device array of
- * dw_apply_noalloc_max_bytes() bytes (64 MiB) that each GPU holds from the first context created on it until the
- * process ends. Every call on a GPU uses that GPU's one array, so calls
+ * hipMalloc). It calls no allocator: for blocks above 512 sites, and for x
+ * and y that do overlap, the internal-layout copies of x and y use a fixed
+ * device array of dw_apply_noalloc_max_bytes() bytes (64 MiB) that each GPU
+ * holds from the first context created on it until the process ends. Every call on a GPU uses that GPU's one array, so calls
  * that overlap on one GPU (different streams, or threads) race and must be
  * serialised by the caller. Whatever the block, a call needs
- * 2 * nrhs * V * 192 bytes (plus alignment) within that size: DW_EINVAL beyond the limit, before any GPU work. Asynchronous on `stream`. */
+ * 2 * nrhs * V * 192 bytes (plus alignment) within that size: DW_EINVAL
+ * beyond the limit, before any GPU work. Asynchronous on `stream`. */
 dw_status dw_apply_noalloc(dw_field field, double m0, const double* x, double* y, int32_t nrhs, hipStream_t stream);
 size_t dw_apply_noalloc_max_bytes(void);
 

@@ -103,6 +103,15 @@ dw_status check_device(dw_ctx ctx) {
   return DW_OK;
 }
 
+// The operator on canonical fields writes y while other workgroups still read x,
+// so it takes fields that lie apart. Overlapping ones (views of one buffer) go
+// through an internal-layout copy of x, which is complete before y is written.
+bool apart(const Geom& g, const double* x, const double* y, int32_t nrhs) {
+  const uintptr_t bytes = (uintptr_t)g.V * 192 * (uintptr_t)nrhs;
+  const uintptr_t a = (uintptr_t)x, b = (uintptr_t)y;
+  return a < b ? b - a >= bytes : a - b >= bytes;
+}
+
 }  // namespace
 
 extern "C" {
@@ -291,7 +300,7 @@ dw_status dw_apply(dw_field f, double m0, const double* x, double* y, int32_t nr
   DW_TRY(check_device(f->ctx));
   ProfScope ps(f->ctx);
   const Geom& g = f->g;
-  if (dslash_canonical_fits(g))
+  if (dslash_canonical_fits(g) && apart(g, x, y, nrhs))
     return launch_dslash_canonical(g, m0, x, f->U[DW_PREC_F64], y, nrhs, stream, f->C[DW_PREC_F64]);
   const size_t n = (size_t)g.V * 12;
   DevBuf xi, yi;
@@ -331,7 +340,7 @@ dw_status dw_apply_noalloc(dw_field f, double m0, const double* x, double* y, in
     return DW_EHIP;
   }
   ProfScope ps(f->ctx);
-  if (dslash_canonical_fits(g))
+  if (dslash_canonical_fits(g) && apart(g, x, y, nrhs))
     return launch_dslash_canonical(g, m0, x, f->U[DW_PREC_F64], y, nrhs, stream, f->C[DW_PREC_F64]);
   const long long n = g.V * 12;
   void* xi = base;
