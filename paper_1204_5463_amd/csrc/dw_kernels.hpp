@@ -28,7 +28,7 @@ struct alignas(16) RmsScale {
   double inverse[2];  // (1 / scale, 0)
 };
 static_assert(offsetof(RmsScale, inverse) % 16 == 0, "a pair is loaded at once");
-// rr[0] <- the sum of G pairs (real part); the scale <- sqrt(n / rr) (1 for rr = 0 or unit)
+// rr[0] <- the sum of G pairs (real part), which lie apart from rr; the scale <- sqrt(n / rr) (1 for rr = 0 or unit)
 dw_status blas_rms_scale(const void* partials, int G, long long n, bool unit, double* rr, RmsScale* scale,
                          hipStream_t s);
 // y = alpha[0] * x (alpha a device double)

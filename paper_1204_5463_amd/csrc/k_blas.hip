@@ -449,6 +449,10 @@ dw_status blas_dots(int prec_v, const void* V, long long stride, int ncols, cons
 
 dw_status blas_rms_scale(const void* partials, int G, long long n, bool unit, double* rr, RmsScale* scale,
                          hipStream_t s) {
+  if (partials == rr) {
+    set_error("blas_rms_scale: the sum would replace a partial");
+    return DW_EINVAL;
+  }
   KTimer kt(DW_K_REDUCE, s);
   hipLaunchKernelGGL(k_rms_scale, 1, kThreads, 0, s, (const s64*)partials, G, (double)n, unit, rr, scale);
   DW_CHECK_LAUNCH();

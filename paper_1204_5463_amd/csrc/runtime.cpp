@@ -483,7 +483,7 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   const long long n = g.V * 12;
   const int prec = sp->storage;
   const int zprec = prec == DW_PREC_F64 ? DW_PREC_F64 : DW_PREC_F32;
-  DevBuf bi, xi, ri, vi, zi, part, hist, scale;
+  DevBuf bi, xi, ri, vi, zi, part, nrm, hist, scale;
   DW_TRY(bi.alloc(f->ctx, (size_t)n * 16, stream));
   DW_TRY(xi.alloc(f->ctx, (size_t)n * 16, stream));
   DW_TRY(ri.alloc(f->ctx, (size_t)n * 16, stream));
@@ -492,6 +492,7 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   // the norms come from the operator's launch where its form gives them
   const bool fused = dslash_canonical_fits(g);
   DW_TRY(part.alloc(f->ctx, (size_t)(kBlasGrid > g.nblk ? kBlasGrid : g.nblk) * 16, stream));
+  if (!fused) DW_TRY(nrm.alloc(f->ctx, 16, stream));
   constexpr int kHist = 512;  // iterations between two looks at the norms
   DW_TRY(hist.alloc(f->ctx, kHist * 16, stream));
   DW_TRY(scale.alloc(f->ctx, sizeof(RmsScale), stream));
@@ -501,13 +502,12 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
     DW_CHECK_HIP(hipStreamSynchronize(stream));
     return DW_OK;
   };
-  auto sqnorm = [&](const void* v, int slot) {
-    return blas_dots(DW_PREC_F64, v, n, 1, (const double*)v, n, part.as<double>(), hist.as<double>() + 2 * slot, 1, 0,
-                     stream);
+  auto sqnorm = [&](const void* v, double* out) {
+    return blas_dots(DW_PREC_F64, v, n, 1, (const double*)v, n, part.as<double>(), out, 1, 0, stream);
   };
   DW_TRY(launch_pack_spinor(g, DW_PREC_F64, b, bi.p, 1.0, 1, stream));
   DW_CHECK_HIP(hipMemsetAsync(xi.p, 0, (size_t)n * 16, stream));
-  DW_TRY(sqnorm(bi.p, 0));
+  DW_TRY(sqnorm(bi.p, hist.as<double>()));
   DW_TRY(fetch(1));
   const double bb = h[0];
   if (!(bb > 0)) {
@@ -524,9 +524,9 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
     DW_TRY(launch_dslash_outer(g, m0, DW_PREC_F64, xi.p, 1.0, f->U[DW_PREC_F64], ri.as<double>(), bi.as<double>(), 1,
                                1, n, n, stream, nullptr, f->C[DW_PREC_F64], nullptr, 0, nullptr,
                                fused ? part.p : nullptr));
-    if (!fused) DW_TRY(sqnorm(ri.p, slot));
+    if (!fused) DW_TRY(sqnorm(ri.p, nrm.as<double>()));
     DW_TRY(fused ? blas_rms_scale(part.p, g.nblk, n, unit, rr, sc, stream)
-                 : blas_rms_scale(rr, 1, n, unit, rr, sc, stream));
+                 : blas_rms_scale(nrm.p, 1, n, unit, rr, sc, stream));
     if (slot == kHist - 1 || k == niter) {
       DW_TRY(fetch(slot + 1));
       for (int j = 0; j <= slot; ++j) resid[k - slot + j] = sqrt(h[2 * j]) / bnorm;
