@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
       CT h0[3], h1[3], g0[3], g1[3];
       auto wf = [&](int e) { return wl[e]; };
       proj<MU, -1, T>([&](int k) { return rho_s[k * kSV + l]; }, h0, h1);
-      su3_mul<true, T>(wf, h0, h1, g0, g1);
+      su3_mul<true, true, T>(wf, h0, h1, g0, g1);
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         out[a * kST] = g0[a];
@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
         const SZ* zn = zr + (long long)encode_block(g, c2) * 12 * kSV + l - 3 * st;
         proj<MU, +1, T>([&](int k) { return ld<T>(zn + k * kSV); }, h0, h1);
       }
-      su3_mul<false, T>(wf, h0, h1, g0, g1);
+      su3_mul<false, true, T>(wf, h0, h1, g0, g1);
       if constexpr (MU % 2 == 0) recon_halves<MU, +1>(mine, theirs, g0, g1);
       else recon_halves<MU, +1>(theirs, mine, g0, g1);
       __builtin_amdgcn_sched_barrier(0);
@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
         const SZ* zn = zr + (long long)nb * 12 * kSV + n;
         const SG* un = U + ((long long)nb * 36 + MU * 9) * kSV + n;
         proj<MU, -1, T>([&](int k) { return ld<T>(zn + k * kSV); }, h0, h1);
-        su3_mul<true, T>([&](int e) { return ld<T>(un + e * kSV); }, h0, h1, g0, g1);
+        su3_mul<true, true, T>([&](int e) { return ld<T>(un + e * kSV); }, h0, h1, g0, g1);
       }
       if constexpr (MU % 2 == 0) recon_halves<MU, -1>(mine, theirs, g0, g1);
       else recon_halves<MU, -1>(theirs, mine, g0, g1);
@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
           pb[(3 + a) * kST + tid] = h1[a];
         }
         proj<LD, -1, T>(pf, h0, h1);
-        su3_mul<true, T>(wf, h0, h1, g0, g1);
+        su3_mul<true, true, T>(wf, h0, h1, g0, g1);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
           pb[(6 + a) * kST + tid] = g0[a];
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
       {
         auto wf = [&](int e) { return w[0][e]; };
         proj<LN, -1, T>(pf, h0, h1);
-        su3_mul<true, T>(wf, h0, h1, g0, g1);
+        su3_mul<true, true, T>(wf, h0, h1, g0, g1);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
           g0[a] = lane_shift<LN, -1>(g0[a]);
@@ -300,7 +300,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
           h0[a] = lane_shift<LN, +1>(h0[a]);
           h1[a] = lane_shift<LN, +1>(h1[a]);
         }
-        su3_mul<false, T>(wf, h0, h1, g0, g1);
+        su3_mul<false, true, T>(wf, h0, h1, g0, g1);
         if constexpr (LN == 0) recon_halves<LN, +1>(mine, theirs, g0, g1);
         else recon_halves<LN, +1>(theirs, mine, g0, g1);
       }
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
           h0[a] = pb[a * kST + tid + st];
           h1[a] = pb[(3 + a) * kST + tid + st];
         }
-        su3_mul<false, T>([&](int e) { return w[1][e]; }, h0, h1, g0, g1);
+        su3_mul<false, true, T>([&](int e) { return w[1][e]; }, h0, h1, g0, g1);
         if constexpr (LD == 2) recon_halves<LD, +1>(mine, theirs, g0, g1);
         else recon_halves<LD, +1>(theirs, mine, g0, g1);
       }

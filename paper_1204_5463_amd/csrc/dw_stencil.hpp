@@ -44,9 +44,7 @@ template <> struct proj_table<1> { static constexpr int pa = 3, a = CP1, pb = 2,
 template <> struct proj_table<2> { static constexpr int pa = 2, a = CPI, pb = 3, b = CMI, qc = 0, c = CMI, qd = 1, d = CPI; };
 template <> struct proj_table<3> { static constexpr int pa = 2, a = CM1, pb = 3, b = CM1, qc = 0, c = CM1, qd = 1, d = CM1; };
 
-// acc += (1 -/+ g_mu) W psi, where W = U (DIR > 0) or U^+ (DIR < 0). Products
-// are chains of fused multiply-adds into the sum (four per complex product; formed
-// apart and added they take six).
+// acc += (1 -/+ g_mu) W psi, where W = U (DIR > 0) or U^+ (DIR < 0).
 // psi(comp) returns the neighbour spinor component comp = spin*3 + colour,
 // u(e) returns link entry e = a*3 + b.
 template <int MU, int DIR, typename T, typename PsiF, typename UF>
@@ -72,11 +70,11 @@ __device__ __forceinline__ void hop(cplx<T> acc[12], PsiF&& psi, UF&& u) {
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       if constexpr (DIR > 0) {
-        cmac(s0, w[a * 3 + b], h0[b]);
-        cmac(s1, w[a * 3 + b], h1[b]);
+        s0 += w[a * 3 + b] * h0[b];
+        s1 += w[a * 3 + b] * h1[b];
       } else {
-        cmacj(s0, w[b * 3 + a], h0[b]);
-        cmacj(s1, w[b * 3 + a], h1[b]);
+        s0 += cdot(w[b * 3 + a], h0[b]);
+        s1 += cdot(w[b * 3 + a], h1[b]);
       }
     }
     g0[a] = s0;
@@ -104,8 +102,8 @@ __device__ __forceinline__ void proj(PsiF&& psi, cplx<T> h0[3], cplx<T> h1[3]) {
     h1[a] = psi(3 + a) + coef<B>(psi(P::pb * 3 + a));
   }
 }
-// g = W h with W = U (DAG false) or U^+ (DAG true), for both spin rows
-template <bool DAG, typename T, typename UF>
+// g = W h with W = U (DAG false) or U^+ (DAG true), for both spin rows (CHAIN: cmadd)
+template <bool DAG, bool CHAIN, typename T, typename UF>
 __device__ __forceinline__ void su3_mul(UF&& u, const cplx<T> h0[3], const cplx<T> h1[3], cplx<T> g0[3],
                                         cplx<T> g1[3]) {
   cplx<T> w[9];
@@ -117,11 +115,11 @@ __device__ __forceinline__ void su3_mul(UF&& u, const cplx<T> h0[3], const cplx<
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       if constexpr (!DAG) {
-        cmac(s0, w[a * 3 + b], h0[b]);
-        cmac(s1, w[a * 3 + b], h1[b]);
+        cmadd<CHAIN>(s0, w[a * 3 + b], h0[b]);
+        cmadd<CHAIN>(s1, w[a * 3 + b], h1[b]);
       } else {
-        cmacj(s0, w[b * 3 + a], h0[b]);
-        cmacj(s1, w[b * 3 + a], h1[b]);
+        cmaddj<CHAIN>(s0, w[b * 3 + a], h0[b]);
+        cmaddj<CHAIN>(s1, w[b * 3 + a], h1[b]);
       }
     }
     g0[a] = s0;

@@ -78,7 +78,7 @@ __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[
     auto wl = [&](int e) { return w[e]; };
     // backward-hop half spinor for site n + mu: U_mu(n)^+ (1 + g_mu) psi(n)
     proj<MU, -1, T>([&](int k) { return psi[k]; }, h0, h1);
-    su3_mul<true, T>(wl, h0, h1, g0, g1);
+    su3_mul<true, chain_of<SG>, T>(wl, h0, h1, g0, g1);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       c.pb[a * bvol + l] = g0[a];
@@ -93,7 +93,7 @@ __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[
       const int nb = encode_block(g, c2), nl = l - (bm - 1) * st;
       proj<MU, +1, T>([&](int k) { return ld<T>(c.xr + spinor_index(g, nb, k, nl)); }, h0, h1);
     }
-    su3_mul<false, T>(wl, h0, h1, g0, g1);
+    su3_mul<false, chain_of<SG>, T>(wl, h0, h1, g0, g1);
     recon_acc<MU, +1, T>(acc, g0, g1);
   }
   blk_sync<BS == 4 && MU < 3>();
@@ -109,7 +109,7 @@ __device__ __forceinline__ void blk_dir(const BlkCtx<T, SX, SG>& c, cplx<T> acc[
       c2[MU] = (c.bc[MU] == 0) ? g.N[MU] - 1 : c.bc[MU] - 1;
       const int nb = encode_block(g, c2), nl = l + (bm - 1) * st;
       proj<MU, -1, T>([&](int k) { return ld<T>(c.xr + spinor_index(g, nb, k, nl)); }, h0, h1);
-      su3_mul<true, T>([&](int e) { return ld<T>(c.U + gauge_index(g, nb, MU, e, nl)); }, h0, h1, g0, g1);
+      su3_mul<true, chain_of<SG>, T>([&](int e) { return ld<T>(c.U + gauge_index(g, nb, MU, e, nl)); }, h0, h1, g0, g1);
     }
     recon_acc<MU, -1, T>(acc, g0, g1);
   }
