@@ -54,7 +54,8 @@ __device__ __forceinline__ void clover_acc(const SC* __restrict__ Cb, int bvol, 
 // of that chirality, pairs `stride` apart. At FP32 (the
 // two-thread preconditioner) the products are chained: formed apart, 32^3x64 1143 -> 1177
 // us per cycle; at FP64 they are not (1838 -> 1856 us for the smaller error).
-template <typename T, typename SC>
+// TWO: the loads in two batches, 48 registers instead of 72.
+template <typename T, bool TWO, typename SC>
 __device__ __forceinline__ void clover_chi(const SC* __restrict__ c, int stride, const cplx<T> v[6], cplx<T> w[6]) {
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
@@ -64,13 +65,15 @@ __device__ __forceinline__ void clover_chi(const SC* __restrict__ c, int stride,
   }
   int q = 3;
 #pragma unroll
-  for (int i = 0; i < 6; ++i)
+  for (int i = 0; i < 6; ++i) {
+    if (TWO && i == 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = i + 1; j < 6; ++j) {
       const cplx<T> o = ld<T>(c + (q++) * stride);
       cmadd<sizeof(T) == 4>(w[i], o, v[j]);
       cmaddj<sizeof(T) == 4>(w[j], o, v[i]);
     }
+  }
 }
 
 // y += s * C x for one site, with x read through xin(comp) one chirality at

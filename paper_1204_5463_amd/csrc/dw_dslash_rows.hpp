@@ -268,17 +268,12 @@ __global__ void __launch_bounds__(MAXT)
   cplx<T> up[3], lowxy[3], lowzt[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) up[a] = lowxy[a] = lowzt[a] = mk<T>(0, 0);
-  rows::dir<0, CANON, BS>(c, up, lowxy);
-  rows::dir<1, CANON, BS>(c, up, lowxy);
-  rows::dir<2, CANON, BS>(c, up, lowzt);
-  rows::dir<3, CANON, BS>(c, up, lowzt);
-  // spin 2 + r: this lane's z/t sum and the other lane's x/y sum
-#pragma unroll
-  for (int a = 0; a < 3; ++a) lowzt[a] += rows::other_row(lowxy[a]);
-  cplx<T> cu[3], cd[3];
   if constexpr (CLOV) {
-    // lane r takes chirality r (spins 2r and 2r + 1) and the two lanes swap
-    // the spin that the other one stores
+    // -2 C psi opens the sums. Lane r takes chirality r (spins 2r and 2r + 1); the
+    // lanes swap the second of the two, so that up gets spin r and lowxy spin 3 - r.
+    // Here the registers are free and the 18 loads go out in two batches; after the
+    // hops they came one or two at a time (24x16x16x24, 4 sides 138 -> 118 us, one lane
+    // per site 125; 18x16x16x36 with 3x4x4x6 blocks 240 -> 185, 205; 32^3x32 332 -> 329).
     cplx<T> w[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) w[i] = mk<T>(0, 0);
@@ -286,16 +281,23 @@ __global__ void __launch_bounds__(MAXT)
       cplx<T> v[6];
 #pragma unroll
       for (int i = 0; i < 6; ++i) v[i] = ld<T>(xsh + (6 * r + i) * g.bvol + l);
-      clover_chi<T>(Cl + ((long long)b * kCloverPairs + 18 * r) * g.bvol + l, g.bvol, v, w);
+      clover_chi<T, true>(Cl + ((long long)b * kCloverPairs + 18 * r) * g.bvol + l, g.bvol, v, w);
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const cplx<T> give = r ? w[a] : w[3 + a];
-      const cplx<T> got = rows::other_row(give);
-      cu[a] = r ? got : w[a];
-      cd[a] = r ? w[3 + a] : got;
+      const cplx<T> got = rows::other_row(w[3 + a]);
+      up[a] = (T)-2 * (r ? got : w[a]);
+      lowxy[a] = (T)-2 * (r ? w[a] : got);
     }
+    __builtin_amdgcn_sched_barrier(0);
   }
+  rows::dir<0, CANON, BS>(c, up, lowxy);
+  rows::dir<1, CANON, BS>(c, up, lowxy);
+  rows::dir<2, CANON, BS>(c, up, lowzt);
+  rows::dir<3, CANON, BS>(c, up, lowzt);
+  // spin 2 + r: this lane's z/t sum and the other lane's x/y sum
+#pragma unroll
+  for (int a = 0; a < 3; ++a) lowzt[a] += rows::other_row(lowxy[a]);
   double sq = 0;
   if (active) {
     const T half = (T)0.5;
@@ -306,7 +308,6 @@ __global__ void __launch_bounds__(MAXT)
         const int k = 6 * q + 3 * r + a;
         const cplx<T> psi = ld<T>(xsh + k * g.bvol + l);
         cplx<T> acc = q ? lowzt[a] : up[a];
-        if constexpr (CLOV) acc -= (T)2 * (q ? cd[a] : cu[a]);
         cplx<T> d = scale * (diag * psi - half * acc);
         if constexpr (MODE == 1) {
           d = ld<T>(bsrc + (long long)rhs * ys + own(k)) - d;

@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(std::i
       CT c[6];
 #pragma unroll
       for (int k = 0; k < 6; ++k) c[k] = mk<T>(0, 0);
-      clover_chi<T>(Cl + ((long long)b * kCloverPairs + 18 * half) * kSV + l + cofs, kSV, x, c);
+      clover_chi<T, false>(Cl + ((long long)b * kCloverPairs + 18 * half) * kSV + l + cofs, kSV, x, c);
 #pragma unroll
       for (int k = 0; k < 6; ++k) s[k] -= (T)2 * c[k];
     }
