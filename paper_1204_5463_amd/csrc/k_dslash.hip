@@ -8,8 +8,9 @@
 // half spinor that site n + mu needs, and hands it over through LDS
 // (sites on a block's lower face compute theirs from the neighbouring
 // block). Launch order is XCD-aware so neighbouring blocks share an L2.
-// FP64 arithmetic uses two threads per site (dw_dslash_rows.hpp); one thread
-// per site remains for FP32 arithmetic and for FP64 blocks above 512 sites.
+// FP64 arithmetic uses two threads per site (dw_dslash_rows.hpp) on canonical
+// fields and where rows_pay says so; one thread per site remains for the other
+// blocks, those above 512 sites among them, and for FP32 arithmetic.
 // Blocks whose LDS footprint exceeds the CU's 160 KiB fall back to a
 // gather kernel that reads all neighbours through the caches.
 //
@@ -325,13 +326,28 @@ template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV
 dw_status launch_any(const Geom& g, T diag, const SX* x, T scale, const SG* U, SY* y, const SY* b, long long xs,
                      long long ys, int nrhs, const int* rlist, hipStream_t s, const SG* Cl, DCtl dc);
 
-// FP64 arithmetic takes the two-lane form: 118 registers instead of 196, four
-// waves per SIMD instead of two (32^3x64: D x 336 -> 327 us, b - D x 578 ->
-// 564 us in a solve). FP32 arithmetic keeps one lane per site: there the
-// registers do not limit the waves and the two lanes read every link twice
-// (24^3x48, 4 right-hand sides: 280 us with one lane, 348 with two).
+// FP64 arithmetic has the two-lane form: 118 registers instead of 196, four
+// waves per SIMD instead of two (one application, 32^3x64 on 4^4 blocks: 494 -> 467
+// us). FP32 arithmetic keeps one lane per site: there the registers do not limit the
+// waves and the two lanes read every link twice (24^3x48, 4 right-hand sides: 280 us
+// with one lane, 348 with two).
 template <typename T>
 constexpr bool kRows = std::is_same<T, double>::value;
+// Which blocks of the internal layout take it, by the wavefronts of a workgroup.
+// Times of one lane -> two, on 10^5 sites, with 4 right-hand sides, on 10^6 sites:
+//   1-4    81 sites 38.9 -> 36.8, 115 -> 101, 332 -> 321 us; 16 sites 76 -> 46, 281 -> 151,
+//          599 -> 379
+//   5-7    160 sites 39 -> 44, 115 -> 115, 273 -> 272; 192 sites 42 -> 48, 120 -> 123, 297
+//          -> 304: the SIMDs get unequal shares, and one lane fits as many blocks per CU
+//   8-12   240 sites 43.4 -> 40.5, 97 -> 95, 305 -> 303; 320 sites 56 -> 52, 159 -> 145,
+//          352 -> 328: one lane leaves most wave slots of the CU empty
+//   13-16  448 sites 46.4 -> 46.4, 122 -> 123, 252 -> 255; 512 sites 33.0 -> 33.5, 90 -> 93,
+//          285 -> 297, and 17 -> 19 on 16 blocks: a barrier waits for 16 wavefronts
+// On canonical fields it runs for all, in place of three launches (512 sites 57 -> 36).
+bool rows_pay(const Geom& g) {
+  const int waves = rows_threads(g) / 64;
+  return waves <= 4 || (waves >= 8 && waves <= 12);
+}
 
 dim3 grid_for(const Geom& g, int nrhs) {
   return dim3((unsigned)xcd_grid((int)((g.V + kThreads - 1) / kThreads)), (unsigned)nrhs);
@@ -364,7 +380,7 @@ template <typename T, typename SX, typename SG, typename SY, int MODE, bool CLOV
 dw_status launch_any(const Geom& g, T diag, const SX* x, T scale, const SG* U, SY* y, const SY* b, long long xs,
                      long long ys, int nrhs, const int* rlist, hipStream_t s, const SG* Cl, DCtl dc) {
   if constexpr (kRows<T>)
-    if (rows_fits<T, SX>(g))
+    if (rows_fits<T, SX>(g) && (rows_pay(g) || dc.part))
       return launch_rows<T, SX, SG, SY, MODE, CLOV, false>(g, diag, x, scale, U, y, b, xs, ys, nrhs, rlist, s, Cl, dc);
   const size_t lds = blk_lds<T, SX>(g);
   const int threads = ((g.bvol + 63) / 64) * 64;
@@ -382,11 +398,10 @@ dw_status launch_any(const Geom& g, T diag, const SX* x, T scale, const SG* U, S
       DW_CHECK_LAUNCH();
       return DW_OK;
     };
-    if constexpr (!kRows<T>) {  // the two-lane form has taken blocks up to 512 sites
+    if constexpr (!kRows<T>)  // at FP64 the two-lane form has taken 4^4 blocks
       if (blk_by_wave<SX>(g, nrhs)) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 256, 4, CLOV>);
-      if (threads <= 256) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 256, 0, CLOV>);
-      if (threads <= 512) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 512, 0, CLOV>);
-    }
+    if (threads <= 256) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 256, 0, CLOV>);
+    if (threads <= 512) return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 512, 0, CLOV>);
     return launch_t(k_dslash_blk<T, SX, SG, SY, MODE, 1024, 0, CLOV>);
   }
   hipLaunchKernelGGL((k_dslash<T, SX, SG, SY, MODE, CLOV>), grid_for(g, nrhs), kThreads, 0, s, g, diag, x, scale, U,
