@@ -259,8 +259,8 @@ dw_status sap_precondition(dw_field field, double m0, const sap_params* sap, con
  * b, x: canonical spinor arrays (one right-hand side) on the device, no
  * overlap; x receives x_niter. resid: host array of niter + 1 doubles,
  * resid[k] = ||b - D x_k|| / ||b|| (FP64). The call returns when done.
- * An exact solution (zero residual) ends the iteration early, the remaining
- * entries of resid set to 0. DW_EINVAL: niter < 0, b = 0, bad sap_params. */
+ * An exact solution (zero residual) ends the iteration, the remaining entries
+ * of resid set to 0; the host sees it after 8, 16, 32, ... iterations. DW_EINVAL: niter < 0, b = 0, bad sap_params. */
 dw_status sap_solve(dw_field field, double m0, const sap_params* sap, const double* b, double* x, int32_t niter,
                     double* resid, hipStream_t stream);
 

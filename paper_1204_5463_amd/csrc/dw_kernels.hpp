@@ -22,9 +22,10 @@ dw_status blas_dots(int prec_v, const void* V, long long stride, int ncols, cons
                     double* partials, double* out, int ostride, int op, hipStream_t s, const int* gate = nullptr,
                     const int* dn = nullptr, int dadd = 0);
 // A scale on the device and its inverse as a complex coefficient, which
-// blas_combine loads as one 16-byte pair.
+// blas_combine loads as one 16-byte pair; live is a gate, 0 for a sum of 0.
 struct alignas(16) RmsScale {
-  double scale, unused;
+  double scale;
+  int live, unused;
   double inverse[2];  // (1 / scale, 0)
 };
 static_assert(offsetof(RmsScale, inverse) % 16 == 0, "a pair is loaded at once");

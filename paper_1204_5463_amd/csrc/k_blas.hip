@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(kThreads)
     for (int q = 0; q < kThreads / kWave; ++q) a += red[q];
     const double sc = unit || a == 0 ? 1.0 : sqrt(n / a);
     rr[0] = a;
-    *scale = RmsScale{sc, 0.0, {1.0 / sc, 0.0}};
+    *scale = RmsScale{sc, a != 0, 0, {1.0 / sc, 0.0}};
   }
 }
 

@@ -413,15 +413,16 @@ dw_status check_sap_params(const Geom& g, const sap_params* sp) {
 
 // z (accumulator, FP64 for F64 storage else FP32) = M v, where v is already
 // at storage precision in the internal layout. nrhs fields, stride V*12.
+// gate (device, may be null): nothing happens where *gate == 0.
 dw_status sap_apply_internal(dw_field f, double m0, const sap_params* sp, const void* v, void* z, int nrhs,
-                             hipStream_t stream) {
+                             hipStream_t stream, const int* gate = nullptr) {
   const Geom& g = f->g;
   const int prec = sp->storage;
   const long long n = g.V * 12;
   for (int cyc = 0; cyc < sp->ncycles; ++cyc)
     for (int colour = 0; colour < 2; ++colour)
       DW_TRY(launch_sap_colour(g, m0, prec, v, z, f->U[prec], colour, sp->nmr, cyc == 0 && colour == 0 ? 1 : 0, nrhs,
-                               n, n, stream, nullptr, f->C[prec], sp->mr_reduction));
+                               n, n, stream, nullptr, f->C[prec], sp->mr_reduction, gate));
   return DW_OK;
 }
 
@@ -493,12 +494,12 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   const bool fused = dslash_canonical_fits(g);
   DW_TRY(part.alloc(f->ctx, (size_t)(kBlasGrid > g.nblk ? kBlasGrid : g.nblk) * 16, stream));
   if (!fused) DW_TRY(nrm.alloc(f->ctx, 16, stream));
-  constexpr int kHist = 512;  // iterations between two looks at the norms
+  constexpr int kHist = 512;  // norms kept on the device
   DW_TRY(hist.alloc(f->ctx, kHist * 16, stream));
   DW_TRY(scale.alloc(f->ctx, sizeof(RmsScale), stream));
   double h[2 * kHist];
-  auto fetch = [&](int count) -> dw_status {
-    DW_CHECK_HIP(hipMemcpyAsync(h, hist.p, (size_t)count * 16, hipMemcpyDeviceToHost, stream));
+  auto fetch = [&](int slot, int count) -> dw_status {
+    DW_CHECK_HIP(hipMemcpyAsync(h, hist.as<double>() + 2 * slot, (size_t)count * 16, hipMemcpyDeviceToHost, stream));
     DW_CHECK_HIP(hipStreamSynchronize(stream));
     return DW_OK;
   };
@@ -508,7 +509,7 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   DW_TRY(launch_pack_spinor(g, DW_PREC_F64, b, bi.p, 1.0, 1, stream));
   DW_CHECK_HIP(hipMemsetAsync(xi.p, 0, (size_t)n * 16, stream));
   DW_TRY(sqnorm(bi.p, hist.as<double>()));
-  DW_TRY(fetch(1));
+  DW_TRY(fetch(0, 1));
   const double bb = h[0];
   if (!(bb > 0)) {
     set_error("sap_solve: b = 0");
@@ -517,31 +518,39 @@ extern "C" dw_status sap_solve(dw_field f, double m0, const sap_params* sp, cons
   const double bnorm = sqrt(bb);
   const bool unit = prec == DW_PREC_F64;
   RmsScale* const sc = scale.as<RmsScale>();
+  // The host looks at the norms after 8, 16, 32, ... iterations and whenever the
+  // device holds kHist of them (a look leaves the GPU idle for about 50 us). From an
+  // exact solution on the gate is closed: the launches up to the next look
+  // return at once, and x stays.
+  int seen = 0;  // norms fetched
+  const int* gate = nullptr;
   for (int k = 0; k <= niter; ++k) {
     const int slot = k % kHist;
     double* rr = hist.as<double>() + 2 * slot;
     // r = b - D x_k (FP64 links, clover and arithmetic)
     DW_TRY(launch_dslash_outer(g, m0, DW_PREC_F64, xi.p, 1.0, f->U[DW_PREC_F64], ri.as<double>(), bi.as<double>(), 1,
-                               1, n, n, stream, nullptr, f->C[DW_PREC_F64], nullptr, 0, nullptr,
+                               1, n, n, stream, nullptr, f->C[DW_PREC_F64], gate, 0, nullptr,
                                fused ? part.p : nullptr));
     if (!fused) DW_TRY(sqnorm(ri.p, nrm.as<double>()));
     DW_TRY(fused ? blas_rms_scale(part.p, g.nblk, n, unit, rr, sc, stream)
                  : blas_rms_scale(nrm.p, 1, n, unit, rr, sc, stream));
-    if (slot == kHist - 1 || k == niter) {
-      DW_TRY(fetch(slot + 1));
-      for (int j = 0; j <= slot; ++j) resid[k - slot + j] = sqrt(h[2 * j]) / bnorm;
-      if (h[2 * slot] == 0) {
-        for (int j = k + 1; j <= niter; ++j) resid[j] = 0;
+    gate = &sc->live;
+    if (k == niter || slot == kHist - 1 || (k >= 7 && (k & (k + 1)) == 0)) {
+      const int count = k + 1 - seen;
+      DW_TRY(fetch(seen % kHist, count));
+      for (int j = 0; j < count; ++j) resid[seen + j] = sqrt(h[2 * j]) / bnorm;
+      seen = k + 1;
+      if (h[2 * (count - 1)] == 0) {
+        for (int j = seen; j <= niter; ++j) resid[j] = 0;
         break;
       }
     }
     if (k == niter || sp->ncycles == 0) continue;  // M = 0 without cycles
     // x_{k+1} = x_k + M r: the preconditioner input at storage precision,
-    // scaled to unit RMS (M is scale-equivariant), the correction added in FP64.
-    // From r = 0 on M r = 0 and x stays
-    DW_TRY(launch_convert(DW_PREC_F64, ri.p, prec, vi.p, 1.0, n, stream, &sc->scale));
-    DW_TRY(sap_apply_internal(f, m0, sp, vi.p, zi.p, 1, stream));
-    DW_TRY(blas_combine(zprec, zi.p, n, 1, sc->inverse, 1.0, xi.as<double>(), n, stream));
+    // scaled to unit RMS (M is scale-equivariant), the correction added in FP64
+    DW_TRY(launch_convert(DW_PREC_F64, ri.p, prec, vi.p, 1.0, n, stream, &sc->scale, gate));
+    DW_TRY(sap_apply_internal(f, m0, sp, vi.p, zi.p, 1, stream, gate));
+    DW_TRY(blas_combine(zprec, zi.p, n, 1, sc->inverse, 1.0, xi.as<double>(), n, stream, gate));
   }
   DW_TRY(launch_unpack_spinor(g, DW_PREC_F64, xi.p, x, 1.0, 1, stream));
   DW_CHECK_HIP(hipStreamSynchronize(stream));
