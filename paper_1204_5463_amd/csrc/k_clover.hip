@@ -69,6 +69,8 @@ __device__ __forceinline__ long long pick(const long long v[4], int i) {
   return i == 0 ? v[0] : i == 1 ? v[1] : i == 2 ? v[2] : v[3];
 }
 
+// ALL: all four copies; else FP64 only
+template <bool ALL>
 struct CloverOut {
   s64* o64;
   s32* o32;
@@ -77,16 +79,19 @@ struct CloverOut {
   __device__ __forceinline__ void put(long long at, C v, bool on) const {
     if (on) {
       st(o64 + at, v);
-      st(o32 + at, v);
-      st(o16 + at, v);
-      st(obf + at, v);
+      if constexpr (ALL) {
+        st(o32 + at, v);
+        st(o16 + at, v);
+        st(obf + at, v);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   }
 };
 
+template <bool ALL>
 __global__ void __launch_bounds__(kThreads, 2)
-    k_clover_build(Geom g, const s64* __restrict__ U, SigmaBlocks sb, double csw, CloverOut out) {
+    k_clover_build(Geom g, const s64* __restrict__ U, SigmaBlocks sb, double csw, CloverOut<ALL> out) {
   __shared__ double own[9][kThreads], far[9][kThreads];  // handed over; by the list, for its site
   __shared__ long long hereL[kThreads], dnL[3][kThreads], upL[3][kThreads], dnN[3][kThreads];
   __shared__ short list[3][kThreads];  // threads whose n - d is outside the workgroup
@@ -135,7 +140,14 @@ __global__ void __launch_bounds__(kThreads, 2)
     int zero = 0;
     asm volatile("" : "+v"(zero));
     const s64* p = U + ofs + (long long)mu * 9 * g.bvol + zero;
-    return [p, &g](int e) { return ld<double>(p + e * g.bvol); };
+    if constexpr (ALL) {
+      return [p, &g](int e) { return ld<double>(p + e * g.bvol); };
+    } else {  // small blocks: a link's entries share their lines, so it is read at once
+      M3 r;
+#pragma unroll
+      for (int e = 0; e < 9; ++e) r.e[e] = ld<double>(p + e * g.bvol);
+      return [r](int e) { return r.e[e]; };
+    }
   };
   auto whole = [](auto&& f) {
     M3 r;
@@ -304,8 +316,20 @@ SigmaBlocks sigma_blocks() {
 
 dw_status launch_clover_build(const Geom& g, const void* U64, double csw, void* const out[4], hipStream_t s) {
   const unsigned grid = (unsigned)xcd_grid((int)((g.V + kThreads - 1) / kThreads));
-  const CloverOut o{(s64*)out[DW_PREC_F64], (s32*)out[DW_PREC_F32], (s16*)out[DW_PREC_F16], (sbf*)out[DW_PREC_BF16]};
-  hipLaunchKernelGGL(k_clover_build, grid, kThreads, 0, s, g, (const s64*)U64, sigma_blocks(), csw, o);
+  s64* o64 = (s64*)out[DW_PREC_F64];
+  // On blocks of one or two sites a wavefront's store of a pair touches as many lines
+  // as it has lanes, so the other copies are converted from the FP64 one, and a
+  // link is read at once: 16^3x32, one site 429 -> 265 us, 1x1x1x2 blocks 272 -> 233.
+  if (g.bvol <= 2) {
+    hipLaunchKernelGGL(k_clover_build<false>, grid, kThreads, 0, s, g, (const s64*)U64, sigma_blocks(), csw,
+                       CloverOut<false>{o64, nullptr, nullptr, nullptr});
+    DW_CHECK_LAUNCH();
+    for (int p : {DW_PREC_F32, DW_PREC_F16, DW_PREC_BF16})
+      DW_TRY(launch_convert(DW_PREC_F64, o64, p, out[p], 1.0, g.V * kCloverPairs, s));
+    return DW_OK;
+  }
+  hipLaunchKernelGGL(k_clover_build<true>, grid, kThreads, 0, s, g, (const s64*)U64, sigma_blocks(), csw,
+                     CloverOut<true>{o64, (s32*)out[DW_PREC_F32], (s16*)out[DW_PREC_F16], (sbf*)out[DW_PREC_BF16]});
   DW_CHECK_LAUNCH();
   return DW_OK;
 }
