@@ -7,7 +7,7 @@
 // spinor read is done twice, the two lanes' reads of a link entry are one
 // request, and a lane holds half the accumulators. The lower components that
 // row r's hops rebuild are spin 3 - r (x, y hops) and spin 2 + r (z, t hops);
-// the two lanes exchange the x/y sum once at the end and lane r stores spins r
+// the two lanes exchange the x/y sum after the y hops and lane r stores spins r
 // and 2 + r.
 //
 // As in the one-lane form the block's spinor is staged in LDS, every link is
@@ -265,15 +265,23 @@ __global__ void __launch_bounds__(MAXT)
   }
   __syncthreads();
   const rows::Ctx<T, SX, SG> c{g, b, l, r, active, r ? (T)-1 : (T)1, bc, lc, n, xr, xsh, pb, U};
-  cplx<T> up[3], lowxy[3], lowzt[3];
+  cplx<T> up[3], lowxy[3], low[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) up[a] = lowxy[a] = lowzt[a] = mk<T>(0, 0);
+  for (int a = 0; a < 3; ++a) up[a] = lowxy[a] = mk<T>(0, 0);
+  rows::dir<0, CANON, BS>(c, up, lowxy);
+  rows::dir<1, CANON, BS>(c, up, lowxy);
+  // spin 2 + r: the z and t hops go on from the other lane's x/y sum, so that the
+  // hops are added in the order of the one-lane form, to the same bits
+#pragma unroll
+  for (int a = 0; a < 3; ++a) low[a] = rows::other_row(lowxy[a]);
+  rows::dir<2, CANON, BS>(c, up, low);
+  rows::dir<3, CANON, BS>(c, up, low);
   if constexpr (CLOV) {
-    // -2 C psi opens the sums. Lane r takes chirality r (spins 2r and 2r + 1); the
-    // lanes swap the second of the two, so that up gets spin r and lowxy spin 3 - r.
-    // Here the registers are free and the 18 loads go out in two batches; after the
-    // hops they came one or two at a time (24x16x16x24, 4 sides 138 -> 118 us, one lane
-    // per site 125; 18x16x16x36 with 3x4x4x6 blocks 240 -> 185, 205; 32^3x32 332 -> 329).
+    // lane r takes chirality r (spins 2r and 2r + 1) and the lanes swap the spin
+    // that the other one stores. The 18 loads go out in two batches, for which the
+    // registers of lowxy are free by now; one or two at a time, 24x16x16x24 with 4
+    // sides took 138 us instead of 130, 18x16x16x36 with 3x4x4x6 blocks 240 instead of 189.
+    __builtin_amdgcn_sched_barrier(0);
     cplx<T> w[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) w[i] = mk<T>(0, 0);
@@ -285,19 +293,11 @@ __global__ void __launch_bounds__(MAXT)
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const cplx<T> got = rows::other_row(w[3 + a]);
-      up[a] = (T)-2 * (r ? got : w[a]);
-      lowxy[a] = (T)-2 * (r ? w[a] : got);
+      const cplx<T> got = rows::other_row(r ? w[a] : w[3 + a]);
+      up[a] -= (T)2 * (r ? got : w[a]);
+      low[a] -= (T)2 * (r ? w[3 + a] : got);
     }
-    __builtin_amdgcn_sched_barrier(0);
   }
-  rows::dir<0, CANON, BS>(c, up, lowxy);
-  rows::dir<1, CANON, BS>(c, up, lowxy);
-  rows::dir<2, CANON, BS>(c, up, lowzt);
-  rows::dir<3, CANON, BS>(c, up, lowzt);
-  // spin 2 + r: this lane's z/t sum and the other lane's x/y sum
-#pragma unroll
-  for (int a = 0; a < 3; ++a) lowzt[a] += rows::other_row(lowxy[a]);
   double sq = 0;
   if (active) {
     const T half = (T)0.5;
@@ -307,7 +307,7 @@ __global__ void __launch_bounds__(MAXT)
       for (int a = 0; a < 3; ++a) {
         const int k = 6 * q + 3 * r + a;
         const cplx<T> psi = ld<T>(xsh + k * g.bvol + l);
-        cplx<T> acc = q ? lowzt[a] : up[a];
+        const cplx<T> acc = q ? low[a] : up[a];
         cplx<T> d = scale * (diag * psi - half * acc);
         if constexpr (MODE == 1) {
           d = ld<T>(bsrc + (long long)rhs * ys + own(k)) - d;

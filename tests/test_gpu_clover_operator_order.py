@@ -1,4 +1,4 @@
-"""The FP64 operator with the clover term, whose sums open with -2 C psi: rounding
+"""The FP64 operator with the clover term, whose entries are read in two batches: rounding
 error on canonical fields and the internal layout, over blocks of a lane group
 (4^4), of one site, and of a partly filled last group.
 
