@@ -283,7 +283,7 @@ dw_status fgmresdr_solve(dw_field field, double m0, const fgmresdr_params* param
                          int32_t nrhs, dw_solve_stats* stats, hipStream_t stream);
 
 /* ---- small dense steps, on host arrays ----------------------------------------
- * The solver runs these one-wavefront FP64 kernels on its own device data;
+ * The solver runs these one-workgroup FP64 kernels on its own device data;
  * these entry points run the same kernels on host arrays (copied in and out,
  * synchronous on the null stream, temporaries from the context's allocator)
  * so that they can be compared with a reference. Complex numbers are

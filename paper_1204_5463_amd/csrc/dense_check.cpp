@@ -2,7 +2,7 @@
 // they can be compared directly with a reference: the least-squares
 // problem of Section 4.2 and the deflated restart of Section 4.4 (harmonic
 // Ritz pairs of Lemma 1, G_{k+1}, its QR factorisation and H^_k). They run
-// the same one-wavefront kernels the solver launches.
+// the same one-workgroup kernels the solver launches.
 #include <string.h>
 
 #include <hip/hip_runtime.h>

@@ -221,13 +221,13 @@ dw_status launch_convert(int pin, const void* in, int pout, void* out, double sc
 // rlist (device, may be null): the nrhs right-hand-side indices to process.
 // gate (device, may be null): right-hand side r is skipped when gate[r * gstride] == 0.
 // dmass (device, may be null): the mass is read there instead of m0.
+// part (device, may be null): ||y||^2 by blocks, nblk pairs (sum, 0) per right-hand
+// side; mode 1, FP64 x and blocks that dslash_canonical_fits takes.
 dw_status launch_dslash_outer(const Geom& g, double m0, int prec_x, const void* x, double scale, const void* U64,
                               double* y, const double* b, int mode, int nrhs, long long x_rhs_stride,
                               long long y_rhs_stride, hipStream_t s, const int* rlist = nullptr,
                               const void* C64 = nullptr, const int* gate = nullptr, int gstride = 0,
                               const double* dmass = nullptr, void* part = nullptr);
-// part (device, may be null): ||y||^2 by blocks, nblk pairs (sum, 0) per right-hand
-// side; mode 1, FP64 x and blocks that dslash_canonical_fits takes
 // y = D x on canonical FP64 fields, no packing pass; for blocks that
 // dslash_canonical_fits takes
 bool dslash_canonical_fits(const Geom& g);

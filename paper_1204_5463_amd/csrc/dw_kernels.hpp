@@ -70,7 +70,7 @@ dw_status gs_update(int prec_v, void* V, long long stride, int nv, int jcol, int
                     const int* gate = nullptr, const int* dcol = nullptr, int prec_w = DW_PREC_F64);
 
 // ---- small dense FP64 (one workgroup) ---------------------------------------------
-// Scalars block written by dense_step / dense_cycle_end (doubles):
+// Scalars block written by dense_fresh, dense_step2, dense_lsq and dense_deflate (doubles):
 enum {
   kSclHnext = 0,      // h_{j+1,j}
   kSclHinv = 1,       // 1 / h_{j+1,j} (0 on breakdown)

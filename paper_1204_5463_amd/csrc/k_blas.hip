@@ -132,7 +132,6 @@ __global__ void __launch_bounds__(kThreads)
   for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n; i += step) st(x + i, a * ld<double>(x + i));
 }
 
-// x += scale * sum_c coef[c] Z_c
 // The scale of a stationary iteration's next preconditioner input, kept on the
 // device: fetching the norm first left the GPU idle for about 50 us per iteration.
 __global__ void __launch_bounds__(kThreads)
@@ -153,6 +152,7 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
+// x += scale * sum_c coef[c] Z_c
 template <typename SZ>
 __global__ void __launch_bounds__(kThreads)
     k_combine(const SZ* __restrict__ Z, long long stride, int ncols, const s64* __restrict__ coef, double scale,

@@ -262,12 +262,14 @@ size_t blk_lds(const Geom& g) {
 }
 
 // Where the BS = 4 form runs (us, general -> BS = 4): 16-bit storage on all grids (FP16
-// 16^3x32 12.3 -> 11.6, 24^3x48 with 4 right-hand sides 133.6 -> 127.4, with the
-// clover term 62.1 -> 54.7, 32^3x64 130.7 -> 127.4; BF16 154.2 -> 132.9 and 150.0 ->
-// 138.8), FP32 up to 4096 workgroups (16 workgroups 12.5 -> 10.0, 512 19.0 -> 17.1, 2048
-// 50.3 -> 46.4). Beyond, FP32 is bound by traffic and the barriers keep the wavefronts
-// of a block together on its lines (8192 266.1 -> 267.8, 10368 277.4 -> 280.4). The
-// two forms do the same arithmetic, bit for bit.
+// 16^3x32 12.3 -> 11.6, 24^3x48 with 4 right-hand sides 134 -> 127, with the clover
+// term 219 -> 192, 32^3x64 131.5 -> 128; BF16 150 -> 139), FP32 up to 4096 workgroups
+// (16^3x32 512 workgroups 19.0 -> 17.2, 2048 49.0 -> 45.3, 4096 89.0 -> 84.3; 24^3x48 2592
+// 79.9 -> 76.5). Beyond, it depends on the lattice: 16^3x32 5120 110 -> 104, 8192 174 ->
+// 163, 12288 298 -> 301, but 24^3x48 5184 138.8 -> 141.7, 10368 276 -> 281, 32^3x64 8192
+// 263.5 -> 267.4: where the fields leave the memory-side cache, FP32 is bound by traffic and
+// the barriers keep the wavefronts of a block together on its lines. The two forms do
+// the same arithmetic, bit for bit.
 template <typename SX>
 bool blk_by_wave(const Geom& g, int nrhs) {
   return cube4(g) && (sizeof(SX) == 4 || (long long)g.nblk * nrhs <= 4096);
