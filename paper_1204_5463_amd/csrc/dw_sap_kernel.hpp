@@ -1,8 +1,8 @@
 // One colour of the Schwarz alternating procedure (paper Section 2, Alg. 2):
 // the kernel template and its launch-shape selection, instantiated once per
 // storage precision by k_sap_<prec>.hip.
-// FP32 storage on 4^4 blocks, and FP64 storage where split_pays says so, take the
-// two-threads-per-site form of dw_sap_split.hpp instead.
+// FP64 and FP32 storage on 4^4 blocks take the two-threads-per-site form of
+// dw_sap_split.hpp instead.
 //
 // One workgroup per block of the given colour; blocks of one colour do not
 // couple (red/black colouring with an even block count per direction), so
@@ -399,7 +399,7 @@ dw_status launch_m(const Geom& g, double m0, const void* v, void* z, const void*
   // with FP16 links: 380 us with links from L1/L2, 517 us staged).
   const size_t need = (size_t)36 * g.bvol * sizeof(SG) + (size_t)12 * g.bvol * sizeof(cplx<T>) + 512;
   const bool hyper4 = g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4;
-  if constexpr (MAXT == 256 && !std::is_same<SG, s32>::value)  // 4^4 blocks at FP32 are taken by launch_split
+  if constexpr (MAXT == 256 && is_link16<SG>)  // the other storages of 4^4 blocks are taken by launch_split
     if (hyper4 && need > 40 * 1024)
       return launch_t<T, SV, SZ, SG, 256, false, 4, CLOV>(g, m0, v, z, U, colour, nmr, z_zero, nrhs, vs, zs, rlist, s,
                                                           C, red2, gate, gs, dmass);
@@ -420,28 +420,12 @@ namespace dw {
 
 namespace sapk {
 
-// Whether FP64 storage on 4^4 blocks takes the two-thread form. It holds a block's
-// links in registers and fills a CU with one block. That pays where the links come
-// from beyond the L2 (one right-hand side) or every CU has one block at most
-// (16^3x16, 2 sides, nmr 5: one thread 211 us, two 176). With more, the sides of a block
-// find its links in the L2, three blocks share a CU, and one thread is faster: 16^3x32,
-// 4 sides, nmr 2, 5, 8: 421, 605, 785 against 466, 635, 804; 12 sides 1259, 1747, 2273
-// against 1402, 1904, 2405. The clover term has twice the entries to read per step:
-// 4 sides 528, 783, 1043 against 551, 774, 995; 12 sides 1500, 2191, 2937 against 1584,
-// 2244, 2904.
-template <bool CLOV>
-bool split_pays(const Geom& g, int nrhs) {
-  constexpr int kCus = 256;
-  return nrhs <= (CLOV ? 4 : 1) || (long long)g.nbc * nrhs <= kCus;
-}
-
 template <typename T, typename SV, typename SZ, typename SG, bool CLOV>
 dw_status launch_b(const Geom& g, double m0, const void* v, void* z, const void* U, int colour, int nmr, int z_zero,
                    int nrhs, long long vs, long long zs, const int* rlist, hipStream_t s, const void* C,
                    double red2, const int* gate, int gs, const double* dmass) {
   if constexpr (!is_link16<SG>)
-    if (g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4 &&
-        (std::is_same<SG, s32>::value || split_pays<CLOV>(g, nrhs)))
+    if (g.B[0] == 4 && g.B[1] == 4 && g.B[2] == 4 && g.B[3] == 4)
       return launch_split<T, SV, SZ, SG, CLOV>(g, m0, v, z, U, colour, nmr, z_zero, nrhs, vs, zs, rlist, s, C, red2,
                                                gate, gs, dmass);
   if (g.bvol <= 256)

@@ -1,5 +1,5 @@
 // One colour of the Schwarz alternating procedure on 4^4 blocks at FP64 and FP32
-// storage (FP64: see split_pays): two threads per site, each with two of the four directions and their
+// storage: two threads per site, each with two of the four directions and their
 // links in registers. Included by dw_sap_kernel.hpp.
 //
 // With one thread per site the links of a block (147 KB at FP64, 74 KB at FP32)
