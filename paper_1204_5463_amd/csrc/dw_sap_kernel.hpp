@@ -247,12 +247,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(sap_w
   // of the block, x fastest), so an MR step loads only the t links. This cuts
   // the step's link traffic, which would otherwise come from beyond the L2
   // (the links of the blocks in flight exceed it), to a quarter.
-  constexpr int NREG = (BS == 4 && L16 && !CLOV && !LDSL) ? 4 : 0;
-  using XW = std::conditional_t<(NREG > 0), decltype(u_blk(0, 0, 0)), int>;
-  XW ux[NREG > 0 ? NREG : 1][9];
-  if constexpr (NREG > 0) {
+  constexpr bool OWN = BS == 4 && L16 && !CLOV && !LDSL;
+  using XW = std::conditional_t<OWN, decltype(u_blk(0, 0, 0)), int>;
+  XW ux[OWN ? 4 : 1][9];
+  if constexpr (OWN) {
 #pragma unroll
-    for (int d = 0; d < NREG; ++d)
+    for (int d = 0; d < 4; ++d)
 #pragma unroll
       for (int e = 0; e < 9; ++e) ux[d][e] = u_blk(d, e, l);
   }
@@ -262,17 +262,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(sap_w
     cplx<T> p[12];
     T nre = 0, nim = 0, den = 0;
     if (active) {
-      // links loaded one hop ahead where the registers allow it without
-      // losing occupancy (16-bit links, no clover term)
-      constexpr bool AHEAD = BS > 0 && !CLOV;
-      if constexpr (AHEAD && P16)
-        hop_sum_block_unrolled<T, h2v, BS, NREG>(l, [&](int nl, int k) { return rho16[k * bvol + nl]; }, u_blk,
-                                                 p, reinterpret_cast<const XW(*)[9]>(ux));
-      else if constexpr (AHEAD && NREG > 0)
-        hop_sum_block_unrolled<T, LK, BS, NREG>(l, [&](int nl, int k) { return rho_s[k * bvol + nl]; }, u_blk, p,
-                                                reinterpret_cast<const XW(*)[9]>(ux));
-      else if constexpr (AHEAD)
-        hop_sum_block_unrolled<T, LK, BS>(l, [&](int nl, int k) { return rho_s[k * bvol + nl]; }, u_blk, p);
+      if constexpr (OWN && P16)
+        hop_sum_block_unrolled<h2v, BS>(l, [&](int nl, int k) { return rho16[k * bvol + nl]; }, u_blk, p, ux);
+      else if constexpr (OWN)
+        hop_sum_block_unrolled<LK, BS>(l, [&](int nl, int k) { return rho_s[k * bvol + nl]; }, u_blk, p, ux);
       else if constexpr (P16)
         hop_sum_staged<T, false, h2v, BS>(
             g, b, l, bc, lc, [&](int nl, int k) { return rho16[k * bvol + nl]; }, u_blk,

@@ -487,13 +487,11 @@ __device__ __forceinline__ cplx<T> lane_shift(cplx<T> v) {
   return mk<T>(lane_shift<MU, DIR>(v.re), lane_shift<MU, DIR>(v.im));
 }
 
-// One direction of hop_sum_block_unrolled (below). Directions MU < NREG take
-// their links from registers (ux[MU], the lane's own site's links, held across
-// calls): the forward hop uses them directly and the backward hop those of the
-// lane st below (the site n - mu, in the same 16-lane row for x and y of 4^4
-// blocks).
-template <int MU, int BS, int NREG, typename T, typename SG, typename XB, typename UB, typename W>
-__device__ __forceinline__ void block_dir_unrolled(int l, XB& xin_blk, UB& u_blk, cplx<T> acc[12], W wf[9],
+// One direction of hop_sum_block_unrolled (below): the forward hop with the lane's
+// own link, the backward hop with that of the lane st below (the site n - mu, in
+// the same wavefront for x, y and z of 4^4 blocks) or, for t, read again.
+template <int MU, int BS, typename SG, typename XB, typename UB, typename W>
+__device__ __forceinline__ void block_dir_unrolled(int l, XB& xin_blk, UB& u_blk, cplx<float> acc[12], W wf[9],
                                                    const W (*ux)[9]) {
   constexpr int LB = ilog2(BS);
   constexpr int st = 1 << (LB * MU);
@@ -503,53 +501,48 @@ __device__ __forceinline__ void block_dir_unrolled(int l, XB& xin_blk, UB& u_blk
   // keep each direction's loads inside its own stretch of code (hoisted,
   // the next directions' links would not fit the register budget)
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (MU < NREG && MU < 3) {
 #pragma unroll
-    for (int e = 0; e < 9; ++e) wb[e] = lane_below<st>(ux[MU][e]);
-  } else {
-#pragma unroll
-    for (int e = 0; e < 9; ++e) wb[e] = u_blk(MU, e, ub);
+  for (int e = 0; e < 9; ++e) {
+    if constexpr (MU < 3) wb[e] = lane_below<st>(ux[MU][e]);
+    else wb[e] = u_blk(MU, e, ub);
   }
   auto do_hop = [&](auto dirc, auto&& psi, auto&& u) {
     constexpr int DIR = decltype(dirc)::value;
     if constexpr (std::is_same<SG, h2v>::value) hop16p<MU, DIR>(acc, psi, u);
-    else if constexpr (is_link16<SG>) hop16<MU, DIR, SG>(acc, psi, u);
-    else hop<MU, DIR, T>(acc, psi, u);
+    else hop16<MU, DIR, SG>(acc, psi, u);
   };
   if (lcm < BS - 1)
     do_hop(std::integral_constant<int, 1>{}, [&](int k) { return xin_blk(l + st, k); }, [&](int e) { return wf[e]; });
   if constexpr (MU < 3) {
 #pragma unroll
-    for (int e = 0; e < 9; ++e) wf[e] = MU + 1 < NREG ? ux[MU + 1][e] : u_blk(MU + 1, e, l);
+    for (int e = 0; e < 9; ++e) wf[e] = ux[MU + 1][e];
   }
   if (lcm > 0)
     do_hop(std::integral_constant<int, -1>{}, [&](int k) { return xin_blk(l - st, k); }, [&](int e) { return wb[e]; });
 }
 
-// In-block hopping sum of D^l (eq. 2) for compile-time BS^4 blocks, with
-// the link loads one hop ahead: per direction the backward hop's links are
-// loaded before the forward hop's arithmetic and the next direction's
-// forward links before the backward hop's, so each hop's L1/L2 latency
-// overlaps the previous hop's work. Sites on the lower face load their own
+// In-block hopping sum of D^l (eq. 2) for compile-time BS^4 blocks of 16-bit
+// links, which the lane holds in registers across calls (ux: its own site's, all
+// four directions). The backward t links are loaded before the forward hop's
+// arithmetic, so that the load overlaps it; sites on the lower face load their own
 // link in place of the (skipped) backward one, which keeps every load inside
 // the block. u_blk(mu, e, local site) returns a link entry as the hop takes it.
 // Directions are unrolled at compile time: every hop is a straight-line
 // body under its lane mask (no switch over the hop index), so the
 // accumulator stays in the same registers from hop to hop.
-template <typename T, typename SG, int BS, int NREG = 0, typename XB, typename UB,
-          typename W = std::remove_cv_t<std::remove_reference_t<decltype(std::declval<UB>()(0, 0, 0))>>>
-__device__ __forceinline__ void hop_sum_block_unrolled(int l, XB&& xin_blk, UB&& u_blk, cplx<T> acc[12],
-                                                       const W (*ux)[9] = nullptr) {
+template <typename SG, int BS, typename XB, typename UB, typename W>
+__device__ __forceinline__ void hop_sum_block_unrolled(int l, XB&& xin_blk, UB&& u_blk, cplx<float> acc[12],
+                                                       const W (*ux)[9]) {
   static_assert(BS > 0 && (BS & (BS - 1)) == 0, "compile-time block side must be a power of two");
 #pragma unroll
-  for (int i = 0; i < 12; ++i) acc[i] = mk<T>(0, 0);
+  for (int i = 0; i < 12; ++i) acc[i] = mk<float>(0, 0);
   W wf[9];
 #pragma unroll
-  for (int e = 0; e < 9; ++e) wf[e] = NREG > 0 ? ux[0][e] : u_blk(0, e, l);
-  block_dir_unrolled<0, BS, NREG, T, SG>(l, xin_blk, u_blk, acc, wf, ux);
-  block_dir_unrolled<1, BS, NREG, T, SG>(l, xin_blk, u_blk, acc, wf, ux);
-  block_dir_unrolled<2, BS, NREG, T, SG>(l, xin_blk, u_blk, acc, wf, ux);
-  block_dir_unrolled<3, BS, NREG, T, SG>(l, xin_blk, u_blk, acc, wf, ux);
+  for (int e = 0; e < 9; ++e) wf[e] = ux[0][e];
+  block_dir_unrolled<0, BS, SG>(l, xin_blk, u_blk, acc, wf, ux);
+  block_dir_unrolled<1, BS, SG>(l, xin_blk, u_blk, acc, wf, ux);
+  block_dir_unrolled<2, BS, SG>(l, xin_blk, u_blk, acc, wf, ux);
+  block_dir_unrolled<3, BS, SG>(l, xin_blk, u_blk, acc, wf, ux);
 }
 
 // Full hopping sum (faces included) for compile-time BS^4 blocks: each hop's
@@ -558,8 +551,8 @@ __device__ __forceinline__ void hop_sum_block_unrolled(int l, XB&& xin_blk, UB&&
 // that the hop arithmetic runs once per hop for all lanes (a branch per
 // source around the whole hop would run it twice on the faces of x, y, z).
 // Links: u_at(block, mu, e, local site); the backward hop's link comes from
-// this block or from the neighbouring block per lane, loaded one hop ahead
-// as in hop_sum_block_unrolled.
+// this block or from the neighbouring block per lane, loaded one hop ahead so
+// that its latency overlaps the previous hop's arithmetic.
 template <typename T, typename SG, int BS, typename XB, typename XH, typename UA>
 __device__ __forceinline__ void hop_sum_halo_ahead(const Geom& g, int b, int l, const int bc[4], XB&& xin_blk,
                                                    XH&& xin_halo, UA&& u_at, cplx<T> acc[12]) {
