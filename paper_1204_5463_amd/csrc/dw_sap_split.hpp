@@ -27,6 +27,13 @@
 // residual ahead of the staging barrier spilled and was slower (nmr 0: 21.6 -> 28.6
 // us). The 16-bit storages keep one thread per site: their links fit the
 // registers there.
+//
+// At FP64 it runs whatever the number of right-hand sides, so that a side's result is
+// the one of a call on its own. With several sides on more blocks than CUs one thread
+// per site would be faster, since the sides find a block's links in the L2 and three
+// blocks share a CU (us per two cycles, nmr 2, 5, 8, one thread -> two): 16^3x32 with 4
+// sides 421, 605, 785 -> 466, 635, 804, with 12 1259, 1747, 2273 -> 1402, 1904, 2405, with 4
+// and the clover term 528, 783, 1043 -> 551, 774, 995; with one side 158, 224 -> 142, 183.
 #pragma once
 
 #include "dw_clover.hpp"
