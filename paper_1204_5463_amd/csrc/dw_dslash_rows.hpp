@@ -17,11 +17,13 @@
 // CANON: x, y and b in the canonical layout (12 contiguous complex numbers per
 // site), so that an application on caller fields needs no packing pass: packing,
 // the operator on the internal layout and unpacking moved 2.7 times the bytes
-// (32^3x64, 12 right-hand sides: 8931 -> 5180 us per application; 8^4: 22.5 ->
+// (32^3x64, 12 right-hand sides: 9097 -> 5263 us per application; 8^4: 22.5 ->
 // 12.0 us, one launch for three and no allocation).
 //
-// Bound: memory. At 12 right-hand sides the launch moves about 0.8 KB per site
-// and right-hand side beyond the L2 (spinor in and out, faces, links shared).
+// Bound: traffic beyond the L2. Counted on 32^3x64 with 12 right-hand sides: 600 B
+// read and 193 B written per site and side (432 B would do: spinor in and out, a
+// twelfth of the links; the rest are faces and links read again), 3.8 TB/s or 0.78 of
+// the copy rate, L2 hits 71%, VALU busy 34% of the SIMD cycles at 3.8 waves per SIMD.
 #pragma once
 
 #include "dw_clover.hpp"

@@ -20,10 +20,12 @@
 //
 // us per colour launch, one thread per site -> now: 16^3x32 nmr 5 FP64 54.5 ->
 // 43.7 (clover 81.9 -> 59.1), FP32 38.8 -> 28.9; 8^4 nmr 4 FP64 34.0 -> 25.6;
-// 32^3x64 nmr 8 FP64 924 -> 796, FP32 496 -> 339 (clover 783 -> 536). Bound: FP64
-// VALU (about 780 instructions per thread and step) and LDS in turn, at two
-// wavefronts per SIMD and one block per CU (registers of the links, 148 KB of
-// LDS); FP32 VALU (710), two blocks per CU. Reading the halo of the block
+// 32^3x64 nmr 8 FP64 924 -> 796, FP32 496 -> 339 (clover 783 -> 536). Bound: FP32 by
+// VALU issue (5661 instructions per wavefront and launch at nmr 8, about 710 per step:
+// busy 86% of the SIMD cycles, two blocks per CU). FP64 (6603, about 780 per step) by the
+// chain of phases in turn, at two wavefronts per SIMD and one block per CU (registers of
+// the links, 148 KB of LDS): on 32^3x64 VALU busy 45%, LDS 40%, on 16^3x32, one block per
+// CU in all, VALU 24%. Reading the halo of the block
 // residual ahead of the staging barrier spilled and was slower (nmr 0: 21.6 -> 28.6
 // us). The 16-bit storages keep one thread per site: their links fit the
 // registers there.
