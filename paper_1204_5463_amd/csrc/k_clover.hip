@@ -22,7 +22,7 @@
 // of a site out of the registers.
 // Bound by the link reads that miss the L2, at two waves per SIMD: counted on 24^3x48
 // 4.0 KB read per site for 576 B of links, 1.15 KB written, 5.2 TB/s together; L2 hits
-// 62%, VALU busy 33%. 24^3x48: the four leaves of each site by themselves, 10 products
+// 63%, VALU busy 33%. 24^3x48: the four leaves of each site by themselves, 10 products
 // and 14 link reads per plane, 840 us -> 660 us. (All sites of the lists at the start
 // instead, spread over the waves: 288 B of spills, 984 us.)
 #include "dw_clover.hpp"
